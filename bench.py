@@ -69,7 +69,7 @@ def sweep_bytes(nx, ny, d):
 # scaled by the same counters on a plain copy): valid only while the kernel
 # sources hash to the value recorded next to the figures.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_sweep_xy_2d_euler_2048_fp64_traffic.md")
-KERNEL_SOURCES = ("za_device.hpp", "za_kernels.hpp", "za_lib.hip")
+KERNEL_SOURCES = ("za_device.hpp", "za_kernels.hpp", "za_launch.hpp", "za_lib.hip")
 
 
 def kernel_sources_sha256():

@@ -65,6 +65,13 @@ inline bool general_weights(const za_problem& p) {
          weight_q(p) != 1.0 || (p.precision == ZA_FP64 && (p.eps > kEpsFastMax || p.eps < kEpsFastMin));
 }
 
+// Every power of the weights is a first or second one (JS, Ai-JS, Ai-Z,
+// squared Z): the kernels without pow().  With L = 0 only p q is used.
+inline bool square_powers(const za_problem& p) {
+  const auto ok = [](double e) { return e == 1.0 || e == 2.0; };
+  return weight_L(p) == 0.0 ? ok(p.p * weight_q(p)) : ok(p.p) && ok(weight_q(p));
+}
+
 template <class T>
 inline za::CfgArg<T> make_cfg(const za_problem& p) {
   za::CfgArg<T> c;
@@ -90,6 +97,15 @@ inline za::CfgArg<T> make_cfg(const za_problem& p) {
 void launch_x_order(za_ctx* c, int mode, const za::SweepArgs& a);
 void launch_y_order(za_ctx* c, int mode, const za::SweepArgs& a);
 int order_y_blocks_per_cu(const za_problem& p);
+
+// Sweeps of WENO-ZA6 (r = 3) with general weights: exponents all 1 or 2
+// (za_square.hip) or any (za_general.hip).
+void launch_x_square(za_ctx* c, int mode, const za::SweepArgs& a);
+void launch_y_square(za_ctx* c, int mode, const za::SweepArgs& a);
+int square_y_blocks_per_cu(const za_problem& p);
+void launch_x_general(za_ctx* c, int mode, const za::SweepArgs& a);
+void launch_y_general(za_ctx* c, int mode, const za::SweepArgs& a);
+int general_y_blocks_per_cu(const za_problem& p);
 
 // Host-side building blocks of the right-hand side (za_lib.hip), shared with
 // other entry points of the library.

@@ -1,0 +1,136 @@
+// Sweep launches of one weight variant (WV), for every system, precision and
+// mode.  Each variant's kernels are instantiated in a translation unit of its
+// own: za_lib.hip (WV_Z1), za_square.hip (WV_SQUARE), za_general.hip
+// (WV_GENERAL).
+#pragma once
+#include "za_internal.hpp"
+
+namespace za {
+
+template <int SYS, int M, class T, int WV>
+static void launch_x_t(za_ctx* c, int mode, const SweepArgs& a) {
+  const CfgArg<T> cfg = make_cfg<T>(c->prob);
+  const int nseg = (a.g.nx + XS_CELLS - 1) / XS_CELLS;
+  const long long waves = (long long)a.g.ny * nseg;
+  const dim3 grid((unsigned)((waves + 3) / 4)), blk(256);
+  if constexpr (SYS == SYS_EULER && sizeof(T) == sizeof(double)) {
+    if (c->ph.pp && (mode == MODE_LX || mode == MODE_STAGE)) {
+      if (mode == MODE_LX)
+        hipLaunchKernelGGL((k_sweep_x_pp<M, MODE_LX, WV>), grid, blk, 0, c->stream, a, cfg);
+      else
+        hipLaunchKernelGGL((k_sweep_x_pp<M, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg);
+      return;
+    }
+  }
+  if constexpr (sizeof(T) == sizeof(double) && WV == WV_Z1) {
+    if ((mode == MODE_LX || mode == MODE_STAGE) && a.xl_chunks > 0) {
+      const long long w = xl_waves(a.g.nx, a.g.ny, a.xl_chunks);
+      const dim3 gl((unsigned)((w + 3) / 4));
+      if (mode == MODE_LX)
+        hipLaunchKernelGGL((k_sweep_xl<SYS, M, WV, MODE_LX>), gl, blk, 0, c->stream, a, cfg);
+      else
+        hipLaunchKernelGGL((k_sweep_xl<SYS, M, WV, MODE_STAGE>), gl, blk, 0, c->stream, a, cfg);
+      return;
+    }
+  }
+  if constexpr (WV == WV_Z1) {
+    switch (mode) {
+      case MODE_FLUX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg); break;
+      case MODE_RHS: hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg); break;
+      case MODE_LX: hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_LX, WV>), grid, blk, 0, c->stream, a, cfg); break;
+      default: hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg); break;
+    }
+  } else {
+    switch (mode) {
+      case MODE_FLUX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg); break;
+      case MODE_RHS: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg); break;
+      case MODE_LX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_LX, WV>), grid, blk, 0, c->stream, a, cfg); break;
+      default: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg); break;
+    }
+  }
+}
+
+template <int SYS, int M, class T, int WV>
+static void launch_y_t(za_ctx* c, int mode, const SweepArgs& a) {
+  const CfgArg<T> cfg = make_cfg<T>(c->prob);
+  const dim3 grid((unsigned)((a.g.nx + 63) / 64), (unsigned)((a.g.ny + a.ytile - 1) / a.ytile)), blk(256);
+  if constexpr (SYS == SYS_EULER && M == 4 && sizeof(T) == sizeof(double)) {
+    if (c->ph.pp && mode == MODE_STAGE) {
+      hipLaunchKernelGGL((k_sweep_y_pp<MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg);
+      return;
+    }
+  }
+  if constexpr (WV == WV_Z1) {
+    switch (mode) {
+      case MODE_FLUX: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg); break;
+      case MODE_RHS: hipLaunchKernelGGL((k_sweep_y<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg); break;
+      default: hipLaunchKernelGGL((k_sweep_y<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg); break;
+    }
+  } else {
+    switch (mode) {
+      case MODE_FLUX: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg); break;
+      case MODE_RHS: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg); break;
+      default: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg); break;
+    }
+  }
+}
+
+template <int WV>
+void launch_x_wv(za_ctx* c, int mode, const SweepArgs& a) {
+  const bool f32 = c->prob.precision == ZA_FP32_RECON;
+#define ZA_X(SYS, M) (f32 ? launch_x_t<SYS, M, float, WV>(c, mode, a) : launch_x_t<SYS, M, double, WV>(c, mode, a))
+  switch (c->prob.system) {
+    case ZA_EULER:
+      if (c->prob.dim == 1) ZA_X(SYS_EULER, 3); else ZA_X(SYS_EULER, 4);
+      break;
+    case ZA_ADVECTION: ZA_X(SYS_ADV, 1); break;
+    case ZA_BURGERS: ZA_X(SYS_BURGERS, 1); break;
+    default: ZA_X(SYS_BUCKLEY, 1); break;
+  }
+#undef ZA_X
+}
+
+template <int WV>
+void launch_y_wv(za_ctx* c, int mode, const SweepArgs& a) {
+  const bool f32 = c->prob.precision == ZA_FP32_RECON;
+#define ZA_Y(SYS, M) (f32 ? launch_y_t<SYS, M, float, WV>(c, mode, a) : launch_y_t<SYS, M, double, WV>(c, mode, a))
+  switch (c->prob.system) {
+    case ZA_EULER: ZA_Y(SYS_EULER, 4); break;
+    case ZA_ADVECTION: ZA_Y(SYS_ADV, 1); break;
+    case ZA_BURGERS: ZA_Y(SYS_BURGERS, 1); break;
+    default: ZA_Y(SYS_BUCKLEY, 1); break;
+  }
+#undef ZA_Y
+}
+
+// Resident blocks per CU of the y-sweep that a stage of p launches (for the
+// band height); 0 if unknown.
+template <int WV>
+int y_blocks_per_cu_wv(const za_problem& p) {
+  const void* fn;
+  if (p.system != ZA_EULER) {
+    if constexpr (WV == WV_Z1)
+      fn = p.precision == ZA_FP32_RECON ? reinterpret_cast<const void*>(&k_sweep_y<SYS_ADV, 1, float, MODE_STAGE, WV>)
+                                        : reinterpret_cast<const void*>(&k_sweep_y<SYS_ADV, 1, double, MODE_STAGE, WV>);
+    else
+      fn = p.precision == ZA_FP32_RECON
+               ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_ADV, 1, float, MODE_STAGE, WV>)
+               : reinterpret_cast<const void*>(&k_sweep_y_any<SYS_ADV, 1, double, MODE_STAGE, WV>);
+  } else if (p.pp_limiter) {
+    fn = reinterpret_cast<const void*>(&k_sweep_y_pp<MODE_STAGE, WV>);
+  } else {
+    if constexpr (WV == WV_Z1)
+      fn = p.precision == ZA_FP32_RECON
+               ? reinterpret_cast<const void*>(&k_sweep_y<SYS_EULER, 4, float, MODE_STAGE, WV>)
+               : reinterpret_cast<const void*>(&k_sweep_y<SYS_EULER, 4, double, MODE_STAGE, WV>);
+    else
+      fn = p.precision == ZA_FP32_RECON
+               ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_EULER, 4, float, MODE_STAGE, WV>)
+               : reinterpret_cast<const void*>(&k_sweep_y_any<SYS_EULER, 4, double, MODE_STAGE, WV>);
+  }
+  int n = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, 256, 0) != hipSuccess) return 0;
+  return n;
+}
+
+}  // namespace za

@@ -19,6 +19,7 @@
 #include "za.h"
 #include "za_kernels.hpp"
 #include "za_internal.hpp"
+#include "za_launch.hpp"
 
 using namespace za;
 
@@ -142,95 +143,6 @@ static void timed_end(za_ctx* c, int cls) {
   c->events[cls].push_back({c->ev_open[cls], e});
 }
 
-template <int SYS, int M, class T, int WV>
-static void launch_x_t(za_ctx* c, int mode, const SweepArgs& a) {
-  const CfgArg<T> cfg = make_cfg<T>(c->prob);
-  const int nseg = (a.g.nx + XS_CELLS - 1) / XS_CELLS;
-  const long long waves = (long long)a.g.ny * nseg;
-  const dim3 grid((unsigned)((waves + 3) / 4)), blk(256);
-  if constexpr (SYS == SYS_EULER && sizeof(T) == sizeof(double)) {
-    if (c->ph.pp && (mode == MODE_LX || mode == MODE_STAGE)) {
-      if (mode == MODE_LX)
-        hipLaunchKernelGGL((k_sweep_x_pp<M, MODE_LX, WV>), grid, blk, 0, c->stream, a, cfg);
-      else
-        hipLaunchKernelGGL((k_sweep_x_pp<M, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg);
-      return;
-    }
-  }
-  if constexpr (sizeof(T) == sizeof(double) && WV == WV_Z1) {
-    if ((mode == MODE_LX || mode == MODE_STAGE) && a.xl_chunks > 0) {
-      const long long w = xl_waves(a.g.nx, a.g.ny, a.xl_chunks);
-      const dim3 gl((unsigned)((w + 3) / 4));
-      if (mode == MODE_LX)
-        hipLaunchKernelGGL((k_sweep_xl<SYS, M, WV, MODE_LX>), gl, blk, 0, c->stream, a, cfg);
-      else
-        hipLaunchKernelGGL((k_sweep_xl<SYS, M, WV, MODE_STAGE>), gl, blk, 0, c->stream, a, cfg);
-      return;
-    }
-  }
-  if constexpr (WV == WV_Z1) {
-    switch (mode) {
-      case MODE_FLUX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      case MODE_RHS: hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      case MODE_LX: hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_LX, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      default: hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg); break;
-    }
-  } else {
-    switch (mode) {
-      case MODE_FLUX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      case MODE_RHS: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      case MODE_LX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_LX, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      default: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg); break;
-    }
-  }
-}
-
-template <int SYS, int M, class T, int WV>
-static void launch_y_t(za_ctx* c, int mode, const SweepArgs& a) {
-  const CfgArg<T> cfg = make_cfg<T>(c->prob);
-  const dim3 grid((unsigned)((a.g.nx + 63) / 64), (unsigned)((a.g.ny + a.ytile - 1) / a.ytile)), blk(256);
-  if constexpr (SYS == SYS_EULER && M == 4 && sizeof(T) == sizeof(double)) {
-    if (c->ph.pp && mode == MODE_STAGE) {
-      hipLaunchKernelGGL((k_sweep_y_pp<MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg);
-      return;
-    }
-  }
-  if constexpr (WV == WV_Z1) {
-    switch (mode) {
-      case MODE_FLUX: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      case MODE_RHS: hipLaunchKernelGGL((k_sweep_y<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      default: hipLaunchKernelGGL((k_sweep_y<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg); break;
-    }
-  } else {
-    switch (mode) {
-      case MODE_FLUX: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      case MODE_RHS: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      default: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg); break;
-    }
-  }
-}
-
-
-// dispatch on (system, dim, precision, weight variant)
-template <int SYS, int M>
-static void launch_x_sys(za_ctx* c, int mode, const SweepArgs& a) {
-  const bool gp = general_weights(c->prob);
-  if (c->prob.precision == ZA_FP32_RECON) {
-    if (gp) launch_x_t<SYS, M, float, WV_GENERAL>(c, mode, a); else launch_x_t<SYS, M, float, WV_Z1>(c, mode, a);
-  } else {
-    if (gp) launch_x_t<SYS, M, double, WV_GENERAL>(c, mode, a); else launch_x_t<SYS, M, double, WV_Z1>(c, mode, a);
-  }
-}
-template <int SYS, int M>
-static void launch_y_sys(za_ctx* c, int mode, const SweepArgs& a) {
-  const bool gp = general_weights(c->prob);
-  if (c->prob.precision == ZA_FP32_RECON) {
-    if (gp) launch_y_t<SYS, M, float, WV_GENERAL>(c, mode, a); else launch_y_t<SYS, M, float, WV_Z1>(c, mode, a);
-  } else {
-    if (gp) launch_y_t<SYS, M, double, WV_GENERAL>(c, mode, a); else launch_y_t<SYS, M, double, WV_Z1>(c, mode, a);
-  }
-}
-
 void launch_x(za_ctx* c, int mode, const SweepArgs& a) {
   timed_begin(c, 0);
   if (order_of(c->prob) != 3) {
@@ -238,14 +150,9 @@ void launch_x(za_ctx* c, int mode, const SweepArgs& a) {
     timed_end(c, 0);
     return;
   }
-  switch (c->prob.system) {
-    case ZA_EULER:
-      if (c->prob.dim == 1) launch_x_sys<SYS_EULER, 3>(c, mode, a); else launch_x_sys<SYS_EULER, 4>(c, mode, a);
-      break;
-    case ZA_ADVECTION: launch_x_sys<SYS_ADV, 1>(c, mode, a); break;
-    case ZA_BURGERS: launch_x_sys<SYS_BURGERS, 1>(c, mode, a); break;
-    default: launch_x_sys<SYS_BUCKLEY, 1>(c, mode, a); break;
-  }
+  if (!general_weights(c->prob)) launch_x_wv<WV_Z1>(c, mode, a);
+  else if (square_powers(c->prob)) launch_x_square(c, mode, a);
+  else launch_x_general(c, mode, a);
   timed_end(c, 0);
 }
 
@@ -256,12 +163,9 @@ void launch_y(za_ctx* c, int mode, const SweepArgs& a) {
     timed_end(c, 1);
     return;
   }
-  switch (c->prob.system) {
-    case ZA_EULER: launch_y_sys<SYS_EULER, 4>(c, mode, a); break;
-    case ZA_ADVECTION: launch_y_sys<SYS_ADV, 1>(c, mode, a); break;
-    case ZA_BURGERS: launch_y_sys<SYS_BURGERS, 1>(c, mode, a); break;
-    default: launch_y_sys<SYS_BUCKLEY, 1>(c, mode, a); break;
-  }
+  if (!general_weights(c->prob)) launch_y_wv<WV_Z1>(c, mode, a);
+  else if (square_powers(c->prob)) launch_y_square(c, mode, a);
+  else launch_y_general(c, mode, a);
   timed_end(c, 1);
 }
 
@@ -323,19 +227,14 @@ SweepArgs base_args(za_ctx* c) {
 // Rows per y-sweep block: split each 64-column strip into as many tiles as
 // there are resident block slots per strip, so that one round of blocks
 // covers the grid (no tail round at partial occupancy).
-template <class T>
 static int pick_ytile(za_ctx* c) {
   const za_problem& p = c->prob;
   if (p.dim != 2) return 64;
-  int blocks_per_cu = 0, cus = 0;
-  const void* fn = p.system == ZA_EULER
-                       ? reinterpret_cast<const void*>(&k_sweep_y<SYS_EULER, 4, T, MODE_STAGE, WV_Z1>)
-                       : reinterpret_cast<const void*>(&k_sweep_y<SYS_ADV, 1, T, MODE_STAGE, WV_Z1>);
-  if (order_of(p) != 3) {
-    blocks_per_cu = order_y_blocks_per_cu(p);
-  } else if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks_per_cu, fn, 256, 0) != hipSuccess) {
-    blocks_per_cu = 0;
-  }
+  int cus = 0;
+  int blocks_per_cu = order_of(p) != 3      ? order_y_blocks_per_cu(p)
+                      : !general_weights(p) ? y_blocks_per_cu_wv<WV_Z1>(p)
+                      : square_powers(p)    ? square_y_blocks_per_cu(p)
+                                            : general_y_blocks_per_cu(p);
   if (blocks_per_cu < 1) blocks_per_cu = 2;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus < 1)
     cus = 256;
@@ -521,7 +420,7 @@ void init_shape(za_ctx* c, const za_problem* p, hipStream_t stream) {
   c->ph.lf_scalar = p->lf == ZA_LF_SCALAR ? 1 : 0;
   c->ph.pp = p->pp_limiter ? 1 : 0;
   c->red_blocks = (int)std::min<size_t>(RED_BLOCKS_MAX, std::max<size_t>(1, (ncell + 2047) / 2048));
-  c->ytile = p->precision == ZA_FP32_RECON ? pick_ytile<float>(c) : pick_ytile<double>(c);
+  c->ytile = pick_ytile(c);
   c->xl_chunks = pick_xl_chunks(c);
   if (p->dim == 2) {
     c->stage_blocks = ((p->nx + 63) / 64) * ((p->ny + c->ytile - 1) / c->ytile);

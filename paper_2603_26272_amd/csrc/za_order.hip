@@ -16,7 +16,18 @@ template <> struct OrderWaves<4> { enum { x = 3, y = 2 }; };
 template <> struct OrderWaves<5> { enum { x = 2, y = 2 }; };
 
 // Z weights with p = 1 take the occupancy-targeted kernels; Ai, p != 1 and
-// linear weights the general ones.
+// linear weights the general ones (without pow() where every exponent is 1
+// or 2, which covers the flux output of Z weights).
+
+template <int SYS, int M, int R, int WV>
+void x_any(za_ctx* c, int mode, const SweepArgs& a, const CfgArg<double>& cfg, dim3 grid) {
+  switch (mode) {
+    case MODE_FLUX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_FLUX, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
+    case MODE_RHS: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_RHS, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
+    case MODE_LX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_LX, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
+    default: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_STAGE, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
+  }
+}
 
 template <int SYS, int M, int R>
 void x_sys(za_ctx* c, int mode, const SweepArgs& a) {
@@ -33,11 +44,16 @@ void x_sys(za_ctx* c, int mode, const SweepArgs& a) {
     }
     return;
   }
+  if (square_powers(c->prob)) x_any<SYS, M, R, WV_SQUARE>(c, mode, a, cfg, grid);
+  else x_any<SYS, M, R, WV_GENERAL>(c, mode, a, cfg, grid);
+}
+
+template <int SYS, int M, int R, int WV>
+void y_any(za_ctx* c, int mode, const SweepArgs& a, const CfgArg<double>& cfg, dim3 grid) {
   switch (mode) {
-    case MODE_FLUX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_FLUX, WV_GENERAL, R>), grid, blk, 0, c->stream, a, cfg); break;
-    case MODE_RHS: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_RHS, WV_GENERAL, R>), grid, blk, 0, c->stream, a, cfg); break;
-    case MODE_LX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_LX, WV_GENERAL, R>), grid, blk, 0, c->stream, a, cfg); break;
-    default: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_STAGE, WV_GENERAL, R>), grid, blk, 0, c->stream, a, cfg); break;
+    case MODE_FLUX: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, double, MODE_FLUX, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
+    case MODE_RHS: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, double, MODE_RHS, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
+    default: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, double, MODE_STAGE, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
   }
 }
 
@@ -53,11 +69,8 @@ void y_sys(za_ctx* c, int mode, const SweepArgs& a) {
       hipLaunchKernelGGL((k_sweep_y_r<SYS, M, double, MODE_STAGE, WV_Z1, R, YW>), grid, blk, 0, c->stream, a, cfg);
     return;
   }
-  switch (mode) {
-    case MODE_FLUX: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, double, MODE_FLUX, WV_GENERAL, R>), grid, blk, 0, c->stream, a, cfg); break;
-    case MODE_RHS: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, double, MODE_RHS, WV_GENERAL, R>), grid, blk, 0, c->stream, a, cfg); break;
-    default: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, double, MODE_STAGE, WV_GENERAL, R>), grid, blk, 0, c->stream, a, cfg); break;
-  }
+  if (square_powers(c->prob)) y_any<SYS, M, R, WV_SQUARE>(c, mode, a, cfg, grid);
+  else y_any<SYS, M, R, WV_GENERAL>(c, mode, a, cfg, grid);
 }
 
 template <int R>
@@ -104,13 +117,15 @@ void launch_y_order(za_ctx* c, int mode, const SweepArgs& a) {
 // height); 0 if unknown.
 int order_y_blocks_per_cu(const za_problem& p) {
   const void* fn = nullptr;
-  const bool gp = general_weights(p);
+  const bool gp = general_weights(p), sq = gp && square_powers(p);
 #define ZA_YFN(R)                                                                                      \
   (p.system == ZA_EULER                                                                                \
-       ? (gp ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_EULER, 4, double, MODE_STAGE, WV_GENERAL, R>) \
-             : reinterpret_cast<const void*>(&k_sweep_y_r<SYS_EULER, 4, double, MODE_STAGE, WV_Z1, R, OrderWaves<R>::y>)) \
-       : (gp ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_ADV, 1, double, MODE_STAGE, WV_GENERAL, R>)   \
-             : reinterpret_cast<const void*>(&k_sweep_y_r<SYS_ADV, 1, double, MODE_STAGE, WV_Z1, R, OrderWaves<R>::y>)))
+       ? (sq   ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_EULER, 4, double, MODE_STAGE, WV_SQUARE, R>) \
+          : gp ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_EULER, 4, double, MODE_STAGE, WV_GENERAL, R>) \
+               : reinterpret_cast<const void*>(&k_sweep_y_r<SYS_EULER, 4, double, MODE_STAGE, WV_Z1, R, OrderWaves<R>::y>)) \
+       : (sq   ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_ADV, 1, double, MODE_STAGE, WV_SQUARE, R>)   \
+          : gp ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_ADV, 1, double, MODE_STAGE, WV_GENERAL, R>)   \
+               : reinterpret_cast<const void*>(&k_sweep_y_r<SYS_ADV, 1, double, MODE_STAGE, WV_Z1, R, OrderWaves<R>::y>)))
   switch (order_of(p)) {
     case 2: fn = ZA_YFN(2); break;
     case 4: fn = ZA_YFN(4); break;
