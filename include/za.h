@@ -130,7 +130,9 @@ typedef struct {
  * context; on error *out is NULL.  Launch shapes are fixed here; the
  * environment variable ZA_XL_CHUNKS, read at this call, sets the chunks of
  * 64 interfaces per row segment of the looped 2D x-sweep (0: one-shot
- * sweep; results are identical either way). */
+ * sweep; results are identical either way).  1D problems of up to some
+ * ten thousand cells run their steps in one resident launch; ZA_RESIDENT=0
+ * in the environment selects ordinary launches (identical results). */
 za_status za_ctx_create(const za_problem* problem, void* hip_stream, za_ctx** out);
 /* Not from the paper (resource management): synchronise the context's
  * stream, free its workspace and the context.  ZA_ERR_ARG for NULL. */
@@ -178,7 +180,8 @@ za_status za_step(za_ctx* ctx, double* q, double dt, double* dt_used);
  * clipped to land on it (ZA_DT_CFL_H2: n = ceil(T/dt (1 - 1e-12)) equal steps, the
  * last T - (n-1) dt), stopping early after max_steps if max_steps > 0.
  * t_final <= 0: exactly max_steps CFL steps without clipping.  dt and t stay
- * on the device; the host checks progress once per captured chunk of steps.
+ * on the device; the host checks progress once per chunk of steps (32, or
+ * 4096 where the steps run in a resident launch).
  * info (host, may be NULL) receives the step statistics.  Synchronises. */
 za_status za_solve(za_ctx* ctx, double* q, double t_final, int64_t max_steps, za_solve_info* info);
 

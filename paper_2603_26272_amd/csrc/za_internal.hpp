@@ -32,6 +32,14 @@ struct za_ctx {
   hipGraphExec_t graph_exec = nullptr;  // GRAPH_STEPS steps for state graph_q
   const double* graph_q = nullptr;
   int chunk_steps = 0;       // steps per host check in za_solve (0: default)
+  // resident 1D kernels (za_line.hpp): blocks and wavefronts per block (0:
+  // not for this problem), exchange words, the next launch's first tag, and
+  // the wait limit (< 0: default)
+  int line_blocks = 0, line_waves = 0;
+  unsigned long long* line_xch = nullptr;
+  unsigned line_tag = 1;
+  long long line_spin = -1;
+  bool line_ok = true;       // false once a block waited too long
   bool timing = false;
   hipEvent_t ev_open[3] = {nullptr, nullptr, nullptr};
   std::vector<std::pair<hipEvent_t, hipEvent_t>> events[3];
@@ -106,6 +114,16 @@ int square_y_blocks_per_cu(const za_problem& p);
 void launch_x_general(za_ctx* c, int mode, const za::SweepArgs& a);
 void launch_y_general(za_ctx* c, int mode, const za::SweepArgs& a);
 int general_y_blocks_per_cu(const za_problem& p);
+
+// Resident 1D kernels (za_line.hip): the launch shape for p (0 blocks: none),
+// the device bytes of its exchange words and their reset; up to n steps from
+// *init (one block; nullptr: from the control block), and a right-hand side
+// (one block).
+void line_shape(const za_problem& p, int* blocks, int* waves);
+size_t line_bytes(int blocks);
+void line_init(za_ctx* c);
+void launch_line(za_ctx* c, double* q, int64_t n, const za::DevCtl* init);
+void launch_line_rhs(za_ctx* c, const double* q, double* rhs);
 
 // Host-side building blocks of the right-hand side (za_lib.hip), shared with
 // other entry points of the library.

@@ -1,6 +1,8 @@
 // Kernels of the WENO-ZA6 hot path for gfx950: sweeps, wave-speed
 // reductions, RK3 stage updates.
 #pragma once
+#include <cmath>
+
 #include "za_device.hpp"
 
 namespace za {
@@ -41,6 +43,8 @@ struct DevCtl {
   int active;             // 1 while stepping
   int bad;                // non-finite / non-physical state seen
   int last;               // the step in progress lands on t_final
+  int stuck;              // resident kernel: a block waited too long
+  unsigned line_tag;      // resident kernel: first tag of the last launch that ran
   int pad;
 };
 
@@ -59,6 +63,7 @@ struct Phys {
   int dt_rule;            // 0 CFL, 1 CFL h^2
   int lf_scalar;          // 1: one LF speed for every field
   int pp;                 // 1: positivity-preserving flux limiter in stages
+  double bl_root[3];      // Buckley-Leverett: where f'' = 0 (buckley_roots)
 };
 
 // Ghost cells: periodic wrap or transmissive clamp (three per side).
@@ -180,26 +185,32 @@ __device__ __forceinline__ void cell_speeds(const double (&Q)[M], const Phys& ph
 // f'(u) = u (1-u) / (2 D^2), D = u^2 + (1-u)^2/4, is extremal where
 // 10 u^3 - 15 u^2 + 1 = 0 (one root in each of (-1/2, 0), (0, 1/2),
 // (1, 3/2)); the maximum is at an end of the interval or at such a root
-// inside it.  The roots are found by bisection to the last bit.
+// inside it.  The roots are found by bisection to the last bit, once on the
+// host (a device thread takes 10 us over it, and every stage asks).
 __device__ __forceinline__ double buckley_dfdu(double u) {
   const double w = 1.0 - u;
   const double D = fma(u, u, 0.25 * w * w);
   return 0.5 * u * w / (D * D);
 }
-__device__ inline double buckley_max_speed(double lo, double hi) {
-  double best = fmax(fabs(buckley_dfdu(lo)), fabs(buckley_dfdu(hi)));
+__host__ inline void buckley_roots(double (&root)[3]) {
   const double b0[3] = {-0.5, 0.0, 1.0}, b1[3] = {0.0, 0.5, 1.5};
   for (int k = 0; k < 3; ++k) {
     double a = b0[k], c = b1[k];
-    const bool neg_at_a = fma(fma(10.0, a, -15.0), a * a, 1.0) < 0.0;
+    const bool neg_at_a = std::fma(std::fma(10.0, a, -15.0), a * a, 1.0) < 0.0;
     for (int it = 0; it < 200; ++it) {
       const double m = 0.5 * (a + c);
       if (!(m > a && m < c)) break;
-      const bool neg = fma(fma(10.0, m, -15.0), m * m, 1.0) < 0.0;
+      const bool neg = std::fma(std::fma(10.0, m, -15.0), m * m, 1.0) < 0.0;
       if (neg == neg_at_a) a = m; else c = m;
     }
-    if (a > lo && a < hi) best = fmax(best, fabs(buckley_dfdu(a)));
+    root[k] = a;
   }
+}
+__device__ __forceinline__ double buckley_max_speed(double lo, double hi, const double (&root)[3]) {
+  double best = fmax(fabs(buckley_dfdu(lo)), fabs(buckley_dfdu(hi)));
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    if (root[k] > lo && root[k] < hi) best = fmax(best, fabs(buckley_dfdu(root[k])));
   return best;
 }
 
@@ -1028,7 +1039,7 @@ __device__ __forceinline__ void wave_final_body(const double* __restrict__ part,
   const bool bad = !(r[0] < __builtin_huge_val());
   double sx = wave_max(r[0], r[2]), sy = wave_max(r[3], r[5]);
   if (sys == SYS_BUCKLEY) {
-    sx = sy = bad ? 0.0 : buckley_max_speed(-r[1], r[0]);
+    sx = sy = bad ? 0.0 : buckley_max_speed(-r[1], r[0], ph.bl_root);
     ctl->alpha[0][0] = sx;
     ctl->alpha[1][0] = sy;
   } else if (sys == SYS_EULER) {

@@ -102,6 +102,9 @@ size_t za_workspace_bytes(const za_problem* p) {
   const size_t blocks = p->dim == 2 ? (size_t)((p->nx + 63) / 64) * (size_t)((p->ny + 15) / 16)
                                     : (size_t)(((p->nx + XS_CELLS - 1) / XS_CELLS + 3) / 4);
   b += std::max<size_t>(RED_BLOCKS_MAX, blocks) * NPART * sizeof(double) + 4096 + sizeof(DevCtl);
+  int lb, lw;
+  line_shape(*p, &lb, &lw);
+  b += line_bytes(lb);                    // exchange words of the resident 1D kernel
   return b;
 }
 
@@ -391,8 +394,57 @@ static DevCtl fresh_ctl() {
   return v;
 }
 
-void launch_ctl_reset(za_ctx* c) {
-  hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, c->stream, c->ctl, fresh_ctl());
+// The control block that starts a stepping sequence.
+static DevCtl start_ctl(double dt_fixed, double t_final, int64_t max_steps) {
+  DevCtl v = fresh_ctl();
+  v.dt_fixed = dt_fixed;
+  v.t_final = t_final;
+  v.max_steps = max_steps;
+  v.active = 1;
+  return v;
+}
+
+static void launch_ctl(za_ctx* c, const DevCtl& v) {
+  hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, c->stream, c->ctl, v);
+}
+void launch_ctl_reset(za_ctx* c) { launch_ctl(c, fresh_ctl()); }
+
+// The control block after everything enqueued so far (waits for it).
+static za_status read_ctl(za_ctx* c, DevCtl* h) {
+  hipError_t e = hipMemcpyWithStream(h, c->ctl, sizeof(DevCtl), hipMemcpyDeviceToHost, c->stream);
+  if (e != hipSuccess) return hip_fail(c, e, "read control block");
+  return ZA_OK;
+}
+
+// Whether the steps of this context run in the resident 1D kernel (event
+// timing brackets the launches of single kernels instead).
+static bool line_ready(const za_ctx* c) { return c->line_blocks > 0 && c->line_ok && !c->timing; }
+
+// n RK3 steps from the control block (start: from this one instead); with
+// read, *h receives the control block afterwards.  A resident launch of
+// several blocks needs *h to hold the control block before the steps (or
+// start), to go back to if a block waits too long for the others (another
+// kernel kept one from being scheduled): the steps are then repeated, and the
+// context stays with, ordinary launches.
+static za_status advance(za_ctx* c, double* q, int64_t n, const DevCtl* start, bool read, DevCtl* h) {
+  za_status st;
+  if (line_ready(c) && c->line_blocks == 1) {
+    launch_line(c, q, n, start);
+    ZA_CHECK_LAUNCH(c, "step launch");
+    return read ? read_ctl(c, h) : ZA_OK;
+  }
+  const DevCtl before = start ? *start : *h;
+  if (start) launch_ctl(c, *start);
+  if (line_ready(c)) {
+    launch_line(c, q, n, nullptr);
+    ZA_CHECK_LAUNCH(c, "step launch");
+    if ((st = read_ctl(c, h)) != ZA_OK) return st;
+    if (!h->stuck) return ZA_OK;
+    c->line_ok = false;
+    launch_ctl(c, before);
+  }
+  if ((st = enqueue_steps(c, q, n)) != ZA_OK) return st;
+  return read ? read_ctl(c, h) : ZA_OK;
 }
 
 // Everything a context derives from its problem without allocating: the
@@ -419,6 +471,7 @@ void init_shape(za_ctx* c, const za_problem* p, hipStream_t stream) {
   c->ph.dt_rule = p->dt_rule;
   c->ph.lf_scalar = p->lf == ZA_LF_SCALAR ? 1 : 0;
   c->ph.pp = p->pp_limiter ? 1 : 0;
+  buckley_roots(c->ph.bl_root);
   c->red_blocks = (int)std::min<size_t>(RED_BLOCKS_MAX, std::max<size_t>(1, (ncell + 2047) / 2048));
   c->ytile = pick_ytile(c);
   c->xl_chunks = pick_xl_chunks(c);
@@ -434,6 +487,13 @@ void init_shape(za_ctx* c, const za_problem* p, hipStream_t stream) {
   // ZA_STEP_GRAPHS=0 runs the steps of za_solve as direct launches instead
   // of replaying captured step graphs (results are identical)
   if (const char* e = std::getenv("ZA_STEP_GRAPHS")) c->graphs_ok = std::atoi(e) != 0;
+  // 1D problems that fit stay resident for many steps; ZA_RESIDENT=0, or
+  // either variable that selects a form of the step launches, turns that off
+  // (results are identical).  ZA_LINE_SPIN: the wait limit in clock ticks.
+  line_shape(*p, &c->line_blocks, &c->line_waves);
+  const char* e = std::getenv("ZA_RESIDENT");
+  if ((e && std::atoi(e) == 0) || std::getenv("ZA_XL_CHUNKS") || std::getenv("ZA_STEP_GRAPHS")) c->line_blocks = 0;
+  if ((e = std::getenv("ZA_LINE_SPIN"))) c->line_spin = std::atoll(e);
 }
 
 // ---------------------------------------------------------------------------
@@ -460,14 +520,17 @@ za_status za_ctx_create(const za_problem* p, void* stream, za_ctx** out) {
     if ((e = hipMalloc(&ptr, st_bytes)) != hipSuccess) { za_ctx_destroy(c); return ZA_ERR_NOMEM; }
     c->lx = (double*)ptr;
   }
-  if ((e = hipMalloc(&ptr, (size_t)c->part_blocks * NPART * sizeof(double) + 4096)) != hipSuccess) {
+  const size_t part_bytes = (size_t)c->part_blocks * NPART * sizeof(double) + 4096;   // a multiple of 16
+  if ((e = hipMalloc(&ptr, part_bytes + line_bytes(c->line_blocks))) != hipSuccess) {
     za_ctx_destroy(c);
     return ZA_ERR_NOMEM;
   }
   c->part = (double*)ptr;
+  c->line_xch = (unsigned long long*)((char*)ptr + part_bytes);
+  line_init(c);
   if ((e = hipMalloc(&ptr, sizeof(DevCtl))) != hipSuccess) { za_ctx_destroy(c); return ZA_ERR_NOMEM; }
   c->ctl = (DevCtl*)ptr;
-  hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, c->stream, c->ctl, fresh_ctl());
+  launch_ctl_reset(c);
   if ((e = hipGetLastError()) != hipSuccess) { za_ctx_destroy(c); return ZA_ERR_DEVICE; }
   *out = c;
   return ZA_OK;
@@ -499,6 +562,11 @@ za_status za_ctx_set_stream(za_ctx* c, void* stream) {
 za_status za_rhs(za_ctx* c, const double* q, double* rhs) {
   if (!c || !q || !rhs || q == rhs) return ZA_ERR_ARG;
   c->speeds_valid = false;
+  if (line_ready(c) && c->line_blocks == 1) {
+    launch_line_rhs(c, q, rhs);
+    ZA_CHECK_LAUNCH(c, "rhs launch");
+    return ZA_OK;
+  }
   launch_wave(c, q, FIN_RHS, 0);
   SweepArgs a = base_args(c);
   a.q = q;
@@ -528,23 +596,19 @@ za_status za_rhs_fluxes(za_ctx* c, const double* q, double* fx, double* fy) {
   return ZA_OK;
 }
 
-static za_status read_ctl(za_ctx* c, DevCtl* h) {
-  hipError_t e = hipStreamSynchronize(c->stream);
-  if (e != hipSuccess) return hip_fail(c, e, "synchronise");
-  e = hipMemcpy(h, c->ctl, sizeof(DevCtl), hipMemcpyDeviceToHost);
-  if (e != hipSuccess) return hip_fail(c, e, "read control block");
-  return ZA_OK;
-}
-
 za_status za_step(za_ctx* c, double* q, double dt, double* dt_used) {
   if (!c || !q) return ZA_ERR_ARG;
   c->speeds_valid = false;
   if (!(dt > 0.0) && !(dt <= 0.0)) return ZA_ERR_ARG;  // NaN
-  hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, c->stream, c->ctl, fresh_ctl());
-  hipLaunchKernelGGL(k_ctl_arm, dim3(1), dim3(64), 0, c->stream, c->ctl, dt > 0.0 ? dt : 0.0,
-                     std::numeric_limits<double>::infinity(), 1LL);
-  za_status st = enqueue_step(c, q);
-  if (st != ZA_OK) return st;
+  const DevCtl v = start_ctl(dt > 0.0 ? dt : 0.0, std::numeric_limits<double>::infinity(), 1);
+  za_status st;
+  if (line_ready(c) && c->line_blocks == 1) {
+    launch_line(c, q, 1, &v);
+    ZA_CHECK_LAUNCH(c, "step launch");
+  } else {
+    launch_ctl(c, v);
+    if ((st = enqueue_step(c, q)) != ZA_OK) return st;
+  }
   if (dt_used) {
     DevCtl h;
     if ((st = read_ctl(c, &h)) != ZA_OK) return st;
@@ -560,10 +624,12 @@ za_status za_solve(za_ctx* c, double* q, double t_final, int64_t max_steps, za_s
   if (!(t_final > 0.0) && max_steps <= 0) return ZA_ERR_ARG;
   if (t_final != t_final) return ZA_ERR_ARG;
   const auto& p = c->prob;
+  const double inf = std::numeric_limits<double>::infinity();
   DevCtl h;
   za_status st;
-  hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, c->stream, c->ctl, fresh_ctl());
-  const int chunk = c->chunk_steps > 0 ? c->chunk_steps : 32;
+  // steps between host checks: a resident launch retires steps beyond the end
+  // by itself and costs nothing extra per step
+  int64_t chunk = c->chunk_steps > 0 ? c->chunk_steps : (line_ready(c) ? 4096 : 32);
   if (t_final > 0.0 && p.dt_rule == ZA_DT_CFL_H2) {
     // fixed dt = cfl h^2: n equal steps, the last one lands on t_final
     const double h2 = p.dim == 2 ? std::min(c->geom.dx, c->geom.dy) : c->geom.dx;
@@ -572,40 +638,36 @@ za_status za_solve(za_ctx* c, double* q, double t_final, int64_t max_steps, za_s
     int64_t n_run = n;
     if (max_steps > 0 && max_steps < n) n_run = max_steps;
     const int64_t n_equal = std::min<int64_t>(n_run, n - 1);
-    hipLaunchKernelGGL(k_ctl_arm, dim3(1), dim3(64), 0, c->stream, c->ctl, dt,
-                       std::numeric_limits<double>::infinity(), (long long)n_equal);
+    h = start_ctl(dt, inf, n_equal);
+    launch_ctl(c, h);
     for (int64_t s = 0; s < n_equal;) {
-      const int64_t k = std::min<int64_t>(n_equal - s, 64 * (int64_t)chunk);
-      if ((st = enqueue_steps(c, q, k)) != ZA_OK) return st;
+      const int64_t k = std::min<int64_t>(n_equal - s, line_ready(c) ? chunk : 64 * chunk);
+      const bool more = s + k < n_equal;
+      if ((st = advance(c, q, k, nullptr, more, &h)) != ZA_OK) return st;
       s += k;
-      if (s < n_equal) {
-        if ((st = read_ctl(c, &h)) != ZA_OK) return st;
-        if (h.bad) break;
-      }
+      if (more && h.bad) break;
     }
     if (n_run == n) {
       const double last = t_final - (double)(n - 1) * dt;
-      hipLaunchKernelGGL(k_ctl_arm, dim3(1), dim3(64), 0, c->stream, c->ctl, last,
-                         std::numeric_limits<double>::infinity(), (long long)n);
+      hipLaunchKernelGGL(k_ctl_arm, dim3(1), dim3(64), 0, c->stream, c->ctl, last, inf, (long long)n);
       if ((st = enqueue_step(c, q)) != ZA_OK) return st;
     }
     if ((st = read_ctl(c, &h)) != ZA_OK) return st;
     if (n_run == n && !h.bad) h.t = t_final;
   } else {
-    const double tf = t_final > 0.0 ? t_final : std::numeric_limits<double>::infinity();
-    hipLaunchKernelGGL(k_ctl_arm, dim3(1), dim3(64), 0, c->stream, c->ctl, 0.0, tf,
-                       (long long)(max_steps > 0 ? max_steps : 0));
+    const double tf = t_final > 0.0 ? t_final : inf;
+    const DevCtl v = start_ctl(0.0, tf, max_steps > 0 ? max_steps : 0);
     // A fixed step count is enqueued exactly; integrating to t_final
     // enqueues chunks and lets the device retire the steps beyond t_final.
     int64_t enqueued = 0;
     while (true) {
-      int n = chunk;
-      if (t_final <= 0.0) n = (int)std::min<int64_t>(chunk, max_steps - enqueued);
-      if ((st = enqueue_steps(c, q, n)) != ZA_OK) return st;
+      int64_t n = chunk;
+      if (t_final <= 0.0) n = std::min<int64_t>(chunk, max_steps - enqueued);
+      if ((st = advance(c, q, n, enqueued == 0 ? &v : nullptr, true, &h)) != ZA_OK) return st;
       enqueued += n;
-      if ((st = read_ctl(c, &h)) != ZA_OK) return st;
       if (!h.active || h.bad) break;
       if (t_final <= 0.0 && enqueued >= max_steps) break;
+      if (!line_ready(c) && chunk > 32 && c->chunk_steps <= 0) chunk = 32;
     }
   }
   if (info) {

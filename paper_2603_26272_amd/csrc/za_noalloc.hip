@@ -63,6 +63,10 @@ extern "C" za_status za_rhs_noalloc(const za_problem* p, const double* q, double
   if (c.red_blocks > RED_BLOCKS_MAX) return ZA_ERR_ARG;   // the scratch holds RED_BLOCKS_MAX rows
   c.part = reinterpret_cast<double*>(base);
   c.ctl = reinterpret_cast<DevCtl*>(base + kCtlOffset);
+  if (c.line_blocks == 1) {
+    launch_line_rhs(&c, q, rhs);
+    return hipGetLastError() == hipSuccess ? ZA_OK : ZA_ERR_DEVICE;
+  }
   launch_ctl_reset(&c);
   launch_wave(&c, q, FIN_RHS, 0);
   SweepArgs a = base_args(&c);
