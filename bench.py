@@ -49,27 +49,26 @@ def ir_per_rhs(nx, ny):
     return (nx + 1) * ny + nx * (ny + 1)
 
 
-def sweep_flops(nx, ny, d):
-    f = FLOPS_2D[d]
-    nir = (nx + 1) * ny if d == "x" else nx * (ny + 1)
+def stage_flops(nx, ny):
+    """Algorithmic FLOP of one 2D Euler stage (both sweeps in one launch)."""
+    x, y = FLOPS_2D["x"], FLOPS_2D["y"]
     cells = nx * ny
-    return nir * f["interface"] + cells * (f["cell_flux"] + f["cell_update"])
+    return ((nx + 1) * ny * x["interface"] + nx * (ny + 1) * y["interface"]
+            + cells * (x["cell_flux"] + x["cell_update"] + y["cell_flux"] + y["cell_update"]))
 
 
-def sweep_bytes(nx, ny, d):
-    """Algorithmic HBM bytes of one sweep launch, averaged over the three RK3
-    stages (FP64, m = 4, 32 B per cell and array): the x-sweep reads Q (and
-    Q^n in stages 2 and 3) and writes the partial stage ca Q^n + cb (Q + dt
-    L_x); the y-sweep reads Q and that partial stage and writes Q^(s+1)."""
-    cells = nx * ny
-    return cells * 32 * 8 // 3 if d == "x" else cells * 32 * 3
+def stage_bytes(nx, ny):
+    """Algorithmic HBM bytes of one fused stage, averaged over the three RK3
+    stages (FP64, m = 4, 32 B per cell and array): reads Q (and Q^n in stages
+    2 and 3) and writes Q^(s+1)."""
+    return nx * ny * 32 * 8 // 3
 
 
-# Measured HBM traffic of the sweeps (rocprofv3 FETCH_SIZE and WRITE_SIZE,
+# Measured HBM traffic of the stage kernel (rocprofv3 FETCH_SIZE and WRITE_SIZE,
 # scaled by the same counters on a plain copy): valid only while the kernel
 # sources hash to the value recorded next to the figures.
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_sweep_xy_2d_euler_2048_fp64_traffic.md")
-KERNEL_SOURCES = ("za_device.hpp", "za_kernels.hpp", "za_launch.hpp", "za_lib.hip")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_fused_2d_euler_2048_fp64.md")
+KERNEL_SOURCES = ("za_device.hpp", "za_kernels.hpp", "za_fused.hpp", "za_fused.hip", "za_lib.hip")
 
 
 def kernel_sources_sha256():
@@ -435,13 +434,12 @@ def study_orders(torch, Context, n=2048, steps=20):
     for r in (2, 3, 4, 5):
         Pr = P.with_(order=r)
         _, wall, info, avg_ms, counts, _ = run_gpu(Pr, q0, steps, 2, torch, Context)
-        fl = {d: ((n + 1) * n if d == "x" else n * (n + 1)) * FLOPS_2D_ORDER_IR[r] for d in ("x", "y")}
+        fl = ir_per_rhs(n, n) * FLOPS_2D_ORDER_IR[r]
         out["runs"].append({
             "r": r, "order": 2 * r, "steps": steps, "IR_s": ir_step * steps / wall,
-            "ms_per_step": wall / steps * 1e3, "x_ms": avg_ms[0], "y_ms": avg_ms[1],
+            "ms_per_step": wall / steps * 1e3, "stage_ms": avg_ms[1],
             "oracle_flop_per_ir": FLOPS_2D_ORDER_IR[r],
-            "x_tflops_oracle_count": fl["x"] / (avg_ms[0] * 1e-3) / 1e12,
-            "y_tflops_oracle_count": fl["y"] / (avg_ms[1] * 1e-3) / 1e12})
+            "tflops_oracle_count": fl / (avg_ms[1] * 1e-3) / 1e12})
     for r in (2, 3, 4, 5):
         row = {"r": r, "linf": []}
         for m in (16, 32, 64):
@@ -648,23 +646,18 @@ def main():
     ms_step = wall / args.steps * 1e3
     log(f"FP64 {value:.4g} IR/s, {ms_step:.4f} ms/step")
 
-    names = ["x-sweep", "y-sweep", "wave-speed"]
-    dom = 0 if avg_ms[0] >= avg_ms[1] else 1
-    d = "x" if dom == 0 else "y"
-    fl = sweep_flops(nx, ny, d)
-    achieved = fl / (avg_ms[dom] * 1e-3) / 1e12
-    kname = "k_sweep_xl" if d == "x" else "k_sweep_y"   # the 2D FP64 stage kernels
+    fl = stage_flops(nx, ny)
+    achieved = fl / (avg_ms[1] * 1e-3) / 1e12
     roofline = {"bound": "alu", "achieved": achieved, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
-                "frac": achieved / PEAK_FP64_TFLOPS, "traffic": measured_traffic(kname),
-                "kernel": f"{kname} (2D Euler FP64)",
-                "avg_launch_ms": avg_ms[dom], "launches": counts[dom],
+                "frac": achieved / PEAK_FP64_TFLOPS, "traffic": measured_traffic("k_fused"),
+                "kernel": "k_fused (2D Euler FP64, both sweeps of a stage)",
+                "avg_launch_ms": avg_ms[1], "launches": counts[1],
                 "timing": "HIP events around every launch on the library's stream, in a second run of the "
                           "same steps after the timed one",
                 "algorithmic_flop_per_launch": fl,
-                "algorithmic_bytes_per_launch": sweep_bytes(nx, ny, d)}
-    kernels = {names[k]: {"avg_ms": avg_ms[k], "launches": counts[k]} for k in range(3)}
-    for k, dd in ((0, "x"), (1, "y")):
-        kernels[names[k]]["tflops"] = sweep_flops(nx, ny, dd) / (avg_ms[k] * 1e-3) / 1e12 if avg_ms[k] else None
+                "algorithmic_bytes_per_launch": stage_bytes(nx, ny)}
+    kernels = {"fused-stage": {"avg_ms": avg_ms[1], "launches": counts[1], "tflops": achieved},
+               "wave-speed": {"avg_ms": avg_ms[2], "launches": counts[2]}}
 
     out = {
         "metric": "WENO-ZA6 interface recons/s (2D Euler, FP64 vs FP32) + served p50/p99 latency",
@@ -727,7 +720,7 @@ def main():
 
 
 def fp32_leg(P, q0, q64, args, torch, Context, log, oracle_steps=10):
-    """FP32 reconstruction on the same workload: throughput, the slower sweep
+    """FP32 reconstruction on the same workload: throughput, the stage kernel
     against the FP32 vector peak, and the density error of the FP32 result
     (i) against the FP64 GPU run after the timed steps and (ii) against the
     FP64 oracle after `oracle_steps` steps, next to the FP64 GPU run's own
@@ -739,28 +732,26 @@ def fp32_leg(P, q0, q64, args, torch, Context, log, oracle_steps=10):
     ir_step = 3 * ir_per_rhs(nx, ny)
     P32 = P.fp32()
     q32, wall32, info32, avg32, cnt32, warm32 = run_gpu(P32, q0, args.steps, args.warmup, torch, Context)
-    names = ["x-sweep", "y-sweep", "wave-speed"]
+    names = {1: "fused-stage", 2: "wave-speed"}
     r64 = q64[0].double()
     e = (q32[0].double() - r64).abs()
     res = {"value": ir_step * args.steps / wall32, "unit": "IR/s",
            "ms_per_step": wall32 / args.steps * 1e3,
            "density_err_vs_gpu_fp64": {"steps": args.steps, "l1": float(e.mean()), "linf": float(e.max())},
-           "avg_launch_ms": {names[k]: avg32[k] for k in range(3)},
+           "avg_launch_ms": {names[k]: avg32[k] for k in names},
            "warmup_detail": warm32}
     log(f"FP32 reconstruction {res['value']:.4g} IR/s")
-    dom = 0 if avg32[0] >= avg32[1] else 1
-    d = "x" if dom == 0 else "y"
-    fl = sweep_flops(nx, ny, d)
-    ach = fl / (avg32[dom] * 1e-3) / 1e12
+    fl = stage_flops(nx, ny)
+    ach = fl / (avg32[1] * 1e-3) / 1e12
     res["roofline"] = {"bound": "alu", "achieved": ach, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                       "frac": ach / PEAK_FP32_TFLOPS, "kernel": f"k_sweep_{d} (2D Euler FP32 reconstruction)",
-                       "avg_launch_ms": avg32[dom],
+                       "frac": ach / PEAK_FP32_TFLOPS, "kernel": "k_fused (2D Euler FP32 reconstruction)",
+                       "avg_launch_ms": avg32[1],
                        "note": "FP32 vector peak with packed FP32 issue; the library is built without packed "
                                "FP32 instructions, whose non-packed issue rate equals the FP64 rate (78.6)",
                        "frac_of_unpacked_issue_rate": ach / PEAK_FP64_TFLOPS,
                        "algorithmic_flop_per_launch": fl,
-                       "algorithmic_bytes_per_launch": sweep_bytes(nx, ny, d),
-                       "hbm_GB_s_algorithmic": sweep_bytes(nx, ny, d) / (avg32[dom] * 1e-3) / 1e9}
+                       "algorithmic_bytes_per_launch": stage_bytes(nx, ny),
+                       "hbm_GB_s_algorithmic": stage_bytes(nx, ny) / (avg32[1] * 1e-3) / 1e9}
     # against the FP64 oracle after a few steps
     n = min(oracle_steps, args.steps)
     threads = int(os.environ.get("OMP_NUM_THREADS", "0") or 0) or os.cpu_count() or 1

@@ -125,12 +125,13 @@ typedef struct {
  * Euler systems eq:Euler1D and Section 4.3; eps and p of
  * eq:weight_nonlinear, Section 4).
  * hip_stream: a hipStream_t (NULL = the default stream).  Allocates the
- * workspace (two RK3 stage states, the x-sweep partial RHS in 2D, the
- * reduction partials and a device control block).  *out receives the
- * context; on error *out is NULL.  Launch shapes are fixed here; the
- * environment variable ZA_XL_CHUNKS, read at this call, sets the chunks of
- * 64 interfaces per row segment of the looped 2D x-sweep (0: one-shot
- * sweep; results are identical either way).  1D problems of up to some
+ * workspace (two RK3 stage states, for 2D scalar laws and limited Euler
+ * stages the x-sweep's partial stage, wave-speed rows and device control
+ * blocks).  *out receives the context; on error *out is NULL.  Launch shapes
+ * are fixed here; the environment variable ZA_XL_CHUNKS, read at this call,
+ * sets the chunks of 64 interfaces per row segment of the looped x-sweep
+ * (1D, and 2D scalar laws; 0: one-shot sweep; results are identical either
+ * way).  1D problems of up to some
  * ten thousand cells run their steps in one resident launch; ZA_RESIDENT=0
  * in the environment selects ordinary launches (identical results). */
 za_status za_ctx_create(const za_problem* problem, void* hip_stream, za_ctx** out);
@@ -144,7 +145,7 @@ za_status za_ctx_set_stream(za_ctx* ctx, void* hip_stream);
  * eq:hyperbolic_1D_scalar_h (0 if the problem is invalid). */
 size_t    za_state_count(const za_problem* problem);
 /* Not from the paper (admission control): device bytes the context
- * allocates for this problem (0 if the problem is invalid). */
+ * allocates for this problem, at most (0 if the problem is invalid). */
 size_t    za_workspace_bytes(const za_problem* problem);
 
 /* rhs = L(q) = -(F_{i+1/2} - F_{i-1/2})/dx [- (G_{j+1/2} - G_{j-1/2})/dy]
@@ -191,10 +192,10 @@ za_status za_solve(za_ctx* ctx, double* q, double t_final, int64_t max_steps, za
  * m*nx*ny doubles each, must not overlap; hip_stream: the hipStream_t to
  * enqueue on (NULL = the default stream).  Computes exactly what za_rhs
  * computes, with the same kernels.  Allocates nothing: the wave-speed
- * partials and the control block live in one static device array of 48.25
+ * rows and the control block live in one static device array of 16.25
  * KiB per GPU (held until the process ends), which covers every grid the
  * library accepts (at most 2^31 cells; the reduction pass strides over the
- * cells with at most 1024 blocks).  Every call on a GPU shares that GPU's
+ * cells with at most 256 blocks).  Every call on a GPU shares that GPU's
  * array and overwrites it: calls that overlap on one GPU (from other streams
  * or threads) race, and the caller must serialise them.  Asynchronous; a
  * non-finite state is not reported (za_rhs reports it through a context).
@@ -217,8 +218,9 @@ const char* za_ctx_last_error(const za_ctx* ctx);
  * recent za_rhs/za_step/za_solve kernels, by kernel class, when timing is
  * enabled (za_ctx_set_timing; timing records events around every launch and
  * runs steps without the captured step graphs):
- * out[0] = x-sweep, out[1] = y-sweep(+stage), out[2] = wave-speed reduction;
- * counts[k] = number of launches averaged.  Synchronises. */
+ * out[0] = x-sweep, out[1] = y-sweep(+stage), or the fused 2D Euler stage
+ * (both sweeps in one launch; out[0] then counts none), out[2] = stand-alone
+ * wave-speed pass; counts[k] = number of launches averaged.  Synchronises. */
 za_status za_ctx_set_timing(za_ctx* ctx, int32_t enable);
 za_status za_ctx_kernel_times(za_ctx* ctx, double* avg_ms, int64_t* counts);
 

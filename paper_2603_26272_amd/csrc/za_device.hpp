@@ -455,11 +455,64 @@ __device__ __forceinline__ T split_pair(const T (&w)[2 * R], const T (&g)[2 * R]
 // ---------------------------------------------------------------------------
 template <int M> struct RecLayout;
 template <> struct RecLayout<4> {
-  enum { NF = 8, Q0 = 0, Q1 = 1, Q2 = 2, E = 3, F1 = 4, F2 = 5, F3 = 6, RS = 7 };
+  enum { PRIM = 0, NF = 8, Q0 = 0, Q1 = 1, Q2 = 2, E = 3, F1 = 4, F2 = 5, F3 = 6, RS = 7, UN = 0, P = 0 };
 };
 template <> struct RecLayout<3> {
-  enum { NF = 6, Q0 = 0, Q1 = 1, Q2 = -1, E = 2, F1 = 3, F2 = -1, F3 = 4, RS = 5 };
+  enum { PRIM = 0, NF = 6, Q0 = 0, Q1 = 1, Q2 = -1, E = 2, F1 = 3, F2 = -1, F3 = 4, RS = 5, UN = 0, P = 0 };
 };
+
+// Records of 2D Euler cells that serve both sweep directions, with a layout
+// per direction that names the fields in that sweep's frame.
+//   FP64: rho, m_x, m_y, E, 1/sqrt(rho), u, v, p (8).  The physical fluxes
+//   are formed where they are read (F1 = m_n u_n + p, F2 = m_t u_n, F3 =
+//   (E + p) u_n: four instructions per stencil point, eight of which per
+//   interface the Roe state saves by reading p): with the six flux fields in
+//   LDS instead a block's ring would leave room for two blocks per CU, not
+//   three.
+//   FP32: rho, m_x, m_y, E, F1 F3 per direction, F2 per direction,
+//   1/sqrt(rho) (11), each flux as its own direction's record evaluates it.
+template <class T> struct Layout2;
+template <> struct Layout2<double> {
+  enum { NF = 8 };
+  struct X { enum { PRIM = 1, Q0 = 0, Q1 = 1, Q2 = 2, E = 3, RS = 4, UN = 5, P = 7, F1 = 0, F2 = 0, F3 = 0 }; };
+  struct Y { enum { PRIM = 1, Q0 = 0, Q1 = 2, Q2 = 1, E = 3, RS = 4, UN = 6, P = 7, F1 = 0, F2 = 0, F3 = 0 }; };
+};
+template <> struct Layout2<float> {
+  enum { NF = 11 };
+  struct X { enum { PRIM = 0, Q0 = 0, Q1 = 1, Q2 = 2, E = 3, RS = 7, UN = 0, P = 0, F1 = 4, F2 = 5, F3 = 6 }; };
+  struct Y { enum { PRIM = 0, Q0 = 0, Q1 = 2, Q2 = 1, E = 3, RS = 7, UN = 0, P = 0, F1 = 8, F2 = 9, F3 = 10 }; };
+};
+
+template <class T>
+__device__ __forceinline__ void euler_record2(const double (&qd)[4], T gm1, T* rec, int fs) {
+  typedef typename Layout2<T>::X X;
+  typedef typename Layout2<T>::Y Y;
+  const T q0 = (T)qd[0], q1 = (T)qd[1], q2 = (T)qd[2], E = (T)qd[3];
+  T sq, hr;
+  sqrt_rsq(q0, sq, hr);
+  const T r = hr + hr;          // 1/sqrt(rho)
+  const T ir = r * r;           // 1/rho
+  const T u = q1 * ir, v = q2 * ir;
+  const T px = gm1 * fma(T(-0.5), fma(u, q1, v * q2), E);
+  rec[X::Q0 * fs] = q0;
+  rec[X::Q1 * fs] = q1;
+  rec[X::Q2 * fs] = q2;
+  rec[X::E * fs] = E;
+  rec[X::RS * fs] = r;
+  if constexpr (X::PRIM != 0) {
+    rec[X::UN * fs] = u;
+    rec[Y::UN * fs] = v;
+    rec[X::P * fs] = px;
+  } else {
+    const T py = gm1 * fma(T(-0.5), fma(v, q2, u * q1), E);
+    rec[X::F1 * fs] = fma(q1, u, px);
+    rec[X::F2 * fs] = q2 * u;
+    rec[X::F3 * fs] = (E + px) * u;
+    rec[Y::F1 * fs] = fma(q2, v, py);
+    rec[Y::F2 * fs] = q1 * v;
+    rec[Y::F3 * fs] = (E + py) * v;
+  }
+}
 
 // Build the record of one Euler cell from its (frame-permuted) state.
 template <class T, int M>
@@ -494,11 +547,15 @@ __device__ __forceinline__ void euler_record(const double (&qd)[M], T gm1, T* re
 // The Roe ingredients of one record: sqrt(rho) u_n = m_n r, sqrt(rho) u_t =
 // m_t r and sqrt(rho) H = (E + p) r with r = 1/sqrt(rho) and
 // p = (gamma-1) (E - ((sqrt(rho) u_n)^2 + (sqrt(rho) u_t)^2)/2).
-template <class T, int M>
+template <class T, int M, class Lo = RecLayout<M>>
 __device__ __forceinline__ void roe_side(const T* __restrict__ rec, int fs, int o, T gm1, T& an, T& at, T& hs) {
-  typedef RecLayout<M> Lo;
   const T q1 = rec[Lo::Q1 * fs + o], E = rec[Lo::E * fs + o], r = rec[Lo::RS * fs + o];
   an = q1 * r;
+  if constexpr (Lo::PRIM != 0) {   // the record holds p
+    at = rec[Lo::Q2 * fs + o] * r;
+    hs = (E + rec[Lo::P * fs + o]) * r;
+    return;
+  }
   T ke;
   if (M == 4) {
     at = rec[(M == 4 ? Lo::Q2 : 0) * fs + o] * r;
@@ -545,10 +602,12 @@ __device__ __forceinline__ void char_project(T u, T v, T q2, T k1, T b1, T Q0, T
 //   A-B are applied multiplied by 2c and the matching columns of R divided
 //   by it, which leaves F = R WENO(L f) unchanged).
 // ---------------------------------------------------------------------------
-template <class T, int M, int WV, int R = 3>
+// REREAD: read cell i's flux from its record a second time at the end instead
+// of holding it (8 registers) across the reconstructions; for kernels that
+// would spill otherwise.
+template <class T, int M, int WV, int R = 3, class Lo = RecLayout<M>, bool REREAD = false>
 __device__ __forceinline__ void euler_flux(const T* __restrict__ rec, int fs, const int (&off)[2 * R], T gm1,
                                            const T (&alpha)[M], const WeightCfg<T>& cfg, T (&Fh)[M]) {
-  typedef RecLayout<M> Lo;
 #define ZA_R(f, j) rec[(f) * fs + off[j]]
   // Roe average of the cells R-1 (= i) and R (= i+1) of the stencil:
   // u = (sqrt(rho_l) u_l + sqrt(rho_r) u_r) / (sqrt(rho_l) + sqrt(rho_r)),
@@ -556,8 +615,8 @@ __device__ __forceinline__ void euler_flux(const T* __restrict__ rec, int fs, co
   const T rl = ZA_R(Lo::RS, R - 1), rr = ZA_R(Lo::RS, R);
   const T iw = (rl * rr) * rcp_nr(rl + rr);
   T anl, atl, hsl, anr, atr, hsr;
-  roe_side<T, M>(rec, fs, off[R - 1], gm1, anl, atl, hsl);
-  roe_side<T, M>(rec, fs, off[R], gm1, anr, atr, hsr);
+  roe_side<T, M, Lo>(rec, fs, off[R - 1], gm1, anl, atl, hsl);
+  roe_side<T, M, Lo>(rec, fs, off[R], gm1, anr, atr, hsr);
   const T u = (anl + anr) * iw;
   const T v = M == 4 ? (atl + atr) * iw : T(0);
   const T H = (hsl + hsr) * iw;
@@ -578,6 +637,20 @@ __device__ __forceinline__ void euler_flux(const T* __restrict__ rec, int fs, co
   // indicators' epsilon is scaled by s^2 (beta and tau scale by s^2) and the
   // descaler's mu_0 by s (mu scales by s), so those two fields take
   // epsilon 4 c^2 eps and mu_0 2 c mu_0 (eq:weight_nonlinear, eq:aimu).
+  // state and physical flux of stencil point j
+  const auto point = [&](int j, T& Q0, T& Q1, T& Q2, T& E, T& F1, T& F2, T& F3) {
+    Q0 = ZA_R(Lo::Q0, j); Q1 = ZA_R(Lo::Q1, j); E = ZA_R(Lo::E, j);
+    Q2 = M == 4 ? ZA_R(M == 4 ? Lo::Q2 : 0, j) : T(0);
+    if constexpr (Lo::PRIM != 0) {
+      const T un = ZA_R(Lo::UN, j), p = ZA_R(Lo::P, j);
+      F1 = fma(Q1, un, p);
+      F2 = Q2 * un;
+      F3 = (E + p) * un;
+    } else {
+      F1 = ZA_R(Lo::F1, j); F3 = ZA_R(Lo::F3, j);
+      F2 = M == 4 ? ZA_R(M == 4 ? Lo::F2 : 0, j) : T(0);
+    }
+  };
   if constexpr (WV == WV_Z1 && R == 3) {
     // The projection is linear, so the differences of the characteristic
     // values between neighbouring stencil points are the projections of the
@@ -591,16 +664,12 @@ __device__ __forceinline__ void euler_flux(const T* __restrict__ rec, int fs, co
     // at a time (a scheduling barrier per pair), which keeps the raw values
     // of two points live instead of six.
     T dW[M][5], dG[M][5], Fi[4];   // Fi: the physical flux of cell i
-    T pQ0 = ZA_R(Lo::Q0, 0), pQ1 = ZA_R(Lo::Q1, 0), pE = ZA_R(Lo::E, 0);
-    T pQ2 = M == 4 ? ZA_R(M == 4 ? Lo::Q2 : 0, 0) : T(0);
-    T pF1 = ZA_R(Lo::F1, 0), pF3 = ZA_R(Lo::F3, 0);
-    T pF2 = M == 4 ? ZA_R(M == 4 ? Lo::F2 : 0, 0) : T(0);
+    T pQ0, pQ1, pQ2, pE, pF1, pF2, pF3;
+    point(0, pQ0, pQ1, pQ2, pE, pF1, pF2, pF3);
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-      const T Q0 = ZA_R(Lo::Q0, k + 1), Q1 = ZA_R(Lo::Q1, k + 1), E = ZA_R(Lo::E, k + 1);
-      const T Q2 = M == 4 ? ZA_R(M == 4 ? Lo::Q2 : 0, k + 1) : T(0);
-      const T F1 = ZA_R(Lo::F1, k + 1), F3 = ZA_R(Lo::F3, k + 1);
-      const T F2 = M == 4 ? ZA_R(M == 4 ? Lo::F2 : 0, k + 1) : T(0);
+      T Q0, Q1, Q2, E, F1, F2, F3;
+      point(k + 1, Q0, Q1, Q2, E, F1, F2, F3);
       T w[M], g[M];
       const T dQ1 = Q1 - pQ1;
       char_project<T, M>(u, v, q2, k1, b1, Q0 - pQ0, dQ1, Q2 - pQ2, E - pE, w);
@@ -610,7 +679,7 @@ __device__ __forceinline__ void euler_flux(const T* __restrict__ rec, int fs, co
         dW[f][k] = w[f];
         dG[f][k] = g[f];
       }
-      if (k + 1 == R - 1) { Fi[0] = Q1; Fi[1] = F1; Fi[2] = F2; Fi[3] = F3; }
+      if (!REREAD && k + 1 == R - 1) { Fi[0] = Q1; Fi[1] = F1; Fi[2] = F2; Fi[3] = F3; }
       pQ0 = Q0; pQ1 = Q1; pQ2 = Q2; pE = E; pF1 = F1; pF2 = F2; pF3 = F3;
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -628,6 +697,10 @@ __device__ __forceinline__ void euler_flux(const T* __restrict__ rec, int fs, co
     // and R L = I: F = F(Q_i) + R S / 6, the back-projection below with the
     // factor 1/6 folded into its constants and the acoustic fields unscaled
     // by 1/(2c) as in the direct form.
+    if constexpr (REREAD) {   // not held across the reconstructions (see the template parameter)
+      T Q0, Q2, E;
+      point(R - 1, Q0, Fi[0], Q2, E, Fi[1], Fi[2], Fi[3]);
+    }
     const T k6 = T(1.0 / 6.0);
     const T s03 = (S[0] + S[M - 1]) * (hc * k6);
     const T d30 = T(0.5 / 6.0) * (S[M - 1] - S[0]);
@@ -646,10 +719,8 @@ __device__ __forceinline__ void euler_flux(const T* __restrict__ rec, int fs, co
     T W[M][2 * R], G[M][2 * R];
 #pragma unroll
     for (int j = 0; j < 2 * R; ++j) {
-      const T Q0 = ZA_R(Lo::Q0, j), Q1 = ZA_R(Lo::Q1, j), E = ZA_R(Lo::E, j);
-      const T Q2 = M == 4 ? ZA_R(M == 4 ? Lo::Q2 : 0, j) : T(0);
-      const T F1 = ZA_R(Lo::F1, j), F3 = ZA_R(Lo::F3, j);
-      const T F2 = M == 4 ? ZA_R(M == 4 ? Lo::F2 : 0, j) : T(0);
+      T Q0, Q1, Q2, E, F1, F2, F3;
+      point(j, Q0, Q1, Q2, E, F1, F2, F3);
       {
         T K = fma(u, Q1, -E);
         if (M == 4) K = fma(v, Q2, K);

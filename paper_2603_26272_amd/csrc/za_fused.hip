@@ -1,0 +1,51 @@
+// Fused 2D Euler stages with Z weights at r = 3, and the launch shape of all
+// of them.
+#include "za_fused_launch.hpp"
+
+using namespace za;
+
+// Strips and bands: the band height that minimises the longest CU's work,
+// counted in steps of one wavefront per SIMD.  A block of s steps covers
+// 4 s - 1 rows.  n resident blocks per CU take n s steps of a CU's issue
+// slots, times 1.5 for n = 1 and 1.15 for n = 2, which leave slots idle; a
+// round of blocks adds 2 steps for its start (first loads and records) and
+// the launch 1 more.  (Fitted over grids from 400^2 to 2048^2: FP64 stages
+// take 9.5 us + 3.2 us per step; 1300 x 900: 76 us with the choice below, 98
+// with one block per CU.)
+void fused_shape(const za_problem& p, int* gx, int* gy) {
+  *gx = *gy = 0;
+  if (p.dim != 2 || p.system != ZA_EULER) return;
+  const bool f32 = p.precision == ZA_FP32_RECON;
+  const int r = order_of(p);
+  int res;
+  if (general_weights(p))
+    res = square_powers(p) ? (f32 ? (int)FuWaves<float, WV_SQUARE, 3>::value : (int)FuWaves<double, WV_SQUARE, 3>::value)
+                           : (f32 ? (int)FuWaves<float, WV_GENERAL, 3>::value : (int)FuWaves<double, WV_GENERAL, 3>::value);
+  else
+    res = f32 ? (int)FuWaves<float, WV_Z1, 3>::value
+              : r == 3 ? (int)FuWaves<double, WV_Z1, 3>::value
+                       : r == 2 ? (int)FuWaves<double, WV_Z1, 2>::value : (int)FuWaves<double, WV_Z1, 5>::value;
+  const int strips = (p.nx + FU_COLS - 1) / FU_COLS, cus = 256;
+  double best = -1;
+  for (int s = 1; s <= 4096; ++s) {
+    const int h = FU_NW * s - 1;   // rows of a band of s steps
+    const int nb = (p.ny + h - 1) / h;
+    const long long m = ((long long)strips * nb + cus - 1) / cus;
+    const long long full = m / res, rest = m % res;
+    const double idle = rest == 1 ? 1.5 : (rest == 2 && res > 2 ? 1.15 : 1.0);
+    const double cost = full * (res * s + 2.0) + (rest ? idle * rest * s + 2.0 : 0.0);
+    if (best < 0 || cost < best) { best = cost; *gx = strips; *gy = nb; }
+    if (nb == 1) break;
+  }
+}
+
+void launch_fused(za_ctx* c, int mode, SweepArgs a) {
+  a.ytile = c->fu_gy;
+  a.nblk = c->fu_gx * c->fu_gy;
+  if (order_of(c->prob) != 3) launch_fused_order(c, mode, a);
+  else if (!general_weights(c->prob)) {
+    if (c->prob.precision == ZA_FP32_RECON) launch_fused_t<float, WV_Z1, 3>(c, mode, a);
+    else launch_fused_t<double, WV_Z1, 3>(c, mode, a);
+  } else if (square_powers(c->prob)) launch_fused_square(c, mode, a);
+  else launch_fused_general(c, mode, a);
+}

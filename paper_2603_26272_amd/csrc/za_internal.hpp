@@ -19,14 +19,14 @@ struct za_ctx {
   double* q1 = nullptr;      // RK3 stage 1 state
   double* q2 = nullptr;      // RK3 stage 2 state
   double* lx = nullptr;      // 2D: x-sweep partial RHS
-  double* part = nullptr;    // reduction partials
-  za::DevCtl* ctl = nullptr; // device control block
-  int red_blocks = 1;
+  double* part = nullptr;    // partial sums (za_conserved_sums); the allocation's start
+  unsigned long long* rows = nullptr;   // wave-speed rows: a set per stage, the first current between steps
+  za::DevCtl* ctl = nullptr; // device control block: a copy per stage, the first current between steps
+  int red_blocks = 1, red_threads = 256;   // stand-alone pass
   int ytile = 64;            // y-sweep rows per block
   int xl_chunks = 0;         // looped x-sweep chunks per row segment (0: one-shot sweep)
-  int stage_blocks = 1;      // blocks of the kernel that writes a stage state
-  int part_blocks = 1;       // capacity of `part` in blocks
-  bool speeds_valid = false; // part holds the wave speeds of the current q
+  int fu_gx = 0, fu_gy = 0;  // fused 2D stage: strips (0: not for this problem), bands
+  bool speeds_valid = false; // the rows hold the wave speeds of the current q
   bool graphs_ok = true;     // step graphs usable on this device
   hipStream_t capture_stream = nullptr;
   hipGraphExec_t graph_exec = nullptr;  // GRAPH_STEPS steps for state graph_q
@@ -125,12 +125,20 @@ void line_init(za_ctx* c);
 void launch_line(za_ctx* c, double* q, int64_t n, const za::DevCtl* init);
 void launch_line_rhs(za_ctx* c, const double* q, double* rhs);
 
+// Fused 2D Euler stage (za_fused.hip): launch shape for p (gx = 0: none), and
+// a launch (MODE_STAGE or MODE_RHS).
+void fused_shape(const za_problem& p, int* gx, int* gy);
+void launch_fused(za_ctx* c, int mode, za::SweepArgs a);
+void launch_fused_square(za_ctx* c, int mode, const za::SweepArgs& a);
+void launch_fused_general(za_ctx* c, int mode, const za::SweepArgs& a);
+void launch_fused_order(za_ctx* c, int mode, const za::SweepArgs& a);
+
 // Host-side building blocks of the right-hand side (za_lib.hip), shared with
 // other entry points of the library.
 void init_shape(za_ctx* c, const za_problem* p, hipStream_t stream);
 za::SweepArgs base_args(za_ctx* c);
-void launch_wave(za_ctx* c, const double* q, int kind, int check_active);
+void launch_speeds(za_ctx* c, const double* q, int clear, const za::DevCtl* start);
+za::SweepArgs rhs_args(za_ctx* c, const double* q, double* out);
+void launch_rhs(za_ctx* c, const double* q, double* rhs);
 void launch_x(za_ctx* c, int mode, const za::SweepArgs& a);
 void launch_y(za_ctx* c, int mode, const za::SweepArgs& a);
-// reset the control block c->ctl on c->stream (a kernel, no memset)
-void launch_ctl_reset(za_ctx* c);

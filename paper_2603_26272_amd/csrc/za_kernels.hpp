@@ -43,9 +43,9 @@ struct DevCtl {
   int active;             // 1 while stepping
   int bad;                // non-finite / non-physical state seen
   int last;               // the step in progress lands on t_final
+  int run;                // the stage in progress runs (its second sweep looks here)
   int stuck;              // resident kernel: a block waited too long
   unsigned line_tag;      // resident kernel: first tag of the last launch that ran
-  int pad;
 };
 
 struct Geom {
@@ -114,7 +114,6 @@ __device__ __forceinline__ double scalar_df(double u, double a) {
 // and order independent, so the result is deterministic.
 // ---------------------------------------------------------------------------
 constexpr int NPART = 6;
-constexpr int RED_BLOCKS_MAX = 1024;
 
 __device__ __forceinline__ double wave_max(double a, double b) { return a > b ? a : b; }
 
@@ -227,43 +226,34 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Block-wide maxima of r into dst[0..NPART); every thread of the block calls.
-__device__ __forceinline__ void block_max_store(double (&r)[NPART], double* __restrict__ dst) {
-#pragma unroll
-  for (int i = 0; i < NPART; ++i) {
-    for (int off = 32; off > 0; off >>= 1) r[i] = wave_max(r[i], __shfl_xor(r[i], off, 64));
-  }
-  __shared__ double sm[8][NPART];
-  const int lane = threadIdx.x & 63, wv = wave_id();
-  if (lane == 0) {
-#pragma unroll
-    for (int i = 0; i < NPART; ++i) sm[wv][i] = r[i];
-  }
-  __syncthreads();
-  if (threadIdx.x < NPART) {
-    double v = sm[0][threadIdx.x];
-    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) v = wave_max(v, sm[w][threadIdx.x]);
-    gptr(dst)[threadIdx.x] = v;
-  }
+__device__ __forceinline__ unsigned hi_word(double x) { return (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32); }
+__device__ __forceinline__ unsigned lo_word(double x) { return (unsigned)__builtin_bit_cast(unsigned long long, x); }
+__device__ __forceinline__ double from_words(unsigned lo, unsigned hi) {
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-template <int SYS, int M>
-__global__ __launch_bounds__(256) void k_wave_partial(const double* __restrict__ q, size_t ncell, Phys ph,
-                                                      const DevCtl* ctl, int check_active,
-                                                      double* __restrict__ part) {
-  if (check_active && !ctl->active) return;
-  double r[NPART];
-#pragma unroll
-  for (int i = 0; i < NPART; ++i) r[i] = -__builtin_huge_val();
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < ncell; i += (size_t)gridDim.x * blockDim.x) {
-    double Q[M];
-#pragma unroll
-    for (int c = 0; c < M; ++c) Q[c] = q[c * ncell + i];
-    cell_speeds<SYS, M>(Q, ph, r);
-  }
-  block_max_store(r, part + (size_t)blockIdx.x * NPART);
+// Maxima of NV words over lanes 0 .. LANES - 1 (4, 16 or 64), wave-uniform.
+// Numbers >= 0 (or +inf) order like their bit patterns, so the maximum of
+// such doubles is the largest high word, then the largest low word beside
+// it: one DPP instruction per step where a 64-bit maximum needs three.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned dpp_max_u32(unsigned x) {
+  const unsigned y = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
+  return x > y ? x : y;
 }
-
+template <int LANES, int NV>
+__device__ __forceinline__ void words_max(unsigned (&m)[NV]) {
+#define ZA_STEP(CTRL, ROWS)                                                  \
+  {                                                                          \
+    _Pragma("unroll") for (int i = 0; i < NV; ++i) m[i] = dpp_max_u32<CTRL, ROWS>(m[i]); \
+  }
+  ZA_STEP(0x111, 0xf) ZA_STEP(0x112, 0xf)                   // row_shr 1, 2
+  if (LANES > 4) { ZA_STEP(0x114, 0xf) ZA_STEP(0x118, 0xf) }   // row_shr 4, 8
+  if (LANES > 16) { ZA_STEP(0x142, 0xa) ZA_STEP(0x143, 0xc) }  // row_bcast 15, 31
+#undef ZA_STEP
+#pragma unroll
+  for (int i = 0; i < NV; ++i) m[i] = (unsigned)__builtin_amdgcn_readlane((int)m[i], LANES - 1);
+}
 // ---------------------------------------------------------------------------
 // Records of one sweep direction (see za_device.hpp).  DIR 1 permutes the 2D
 // Euler state into the sweep-normal frame (rho, rho v, rho u, E).
@@ -457,14 +447,270 @@ struct SweepArgs {
   Geom g;
   Phys ph;
   double ca, cb;         // stage: out = ca*qn + cb*(q + dt*L)
-  int check_active;      // stepping: skip when the integration is inactive
+  int check_run;         // without sp_in: skip when ctl->run is 0
+  // stage bookkeeping in the first sweep of a stage (see stage_begin; sp_in
+  // null: the constants are in ctl)
+  const DevCtl* cin;     // control block before this stage (ctl: after it)
+  const unsigned long long* sp_in;   // wave-speed rows of the stage's input
+  int sp_rows;           // ... how many
+  unsigned long long* sp_out;        // rows of the new state (SP_ROWS, atomic maxima)
+  unsigned long long* sp_zero;       // rows to clear for the next stage
+  int nblk;              // blocks of this sweep (which clear sp_zero together)
+  int kind;              // FIN_RHS, or the stage: FIN_STAGE0, FIN_STAGEK, FIN_STAGE2
   int ytile;             // y-sweep: at most this many rows per block (band)
-  double* part;          // MODE_STAGE: per-block wave-speed maxima of the new state
   int xl_chunks;         // looped x-sweep: 64-interface chunks per row segment
 };
 
 template <class T>
 struct CfgArg { WeightCfg<T> w; };
+
+// ---------------------------------------------------------------------------
+// Stage bookkeeping.  A step is its three stage kernels (or pairs of sweeps)
+// and nothing else: the kernel that writes a state folds the state's
+// wave-speed maxima into SP_ROWS rows with atomics, and the first kernel of
+// the next stage reduces those rows itself, in every wavefront, and advances
+// the control block (every block computes it, block 0 stores it: cin ->
+// ctl, one copy per stage).  A separate one-block launch for this took
+// 5.3 us of a 2048^2 stage's 290 and 4.3 of a 128^2 stage's 25; here it takes
+// about 1 us behind the loads of a block's first rows.  Three sets of rows
+// rotate: read, written, cleared for the stage after.  (256 rows: with 64,
+// the 760 blocks of a 2048^2 stage queue at the same lines, 252 against
+// 246 us.)
+//
+// A row holds NPART 64-bit keys (one 64-byte line), ordered like the numbers
+// they stand for; 0 is below every number.
+// ---------------------------------------------------------------------------
+constexpr int SP_ROWS = 256, SP_STRIDE = 8, SP_SET = SP_ROWS * SP_STRIDE;
+constexpr int SP_SETS = 3, CTL_COPIES = 3;   // one per stage of a step
+
+// FIN_STAGE2: the last stage, whose bookkeeping also ends the step.
+enum FinalKind { FIN_RHS = 0, FIN_STAGE0 = 1, FIN_STAGEK = 2, FIN_STAGE2 = 3 };
+
+// A wave-uniform value moved to scalar registers.
+__device__ __forceinline__ double scalar_of(double x) {
+  return from_words((unsigned)__builtin_amdgcn_readfirstlane((int)lo_word(x)),
+                    (unsigned)__builtin_amdgcn_readfirstlane((int)hi_word(x)));
+}
+
+__device__ __forceinline__ unsigned long long speed_key(double x) {
+  const long long s = __builtin_bit_cast(long long, x);
+  return s >= 0 ? (unsigned long long)s | 0x8000000000000000ull : ~(unsigned long long)s;
+}
+__device__ __forceinline__ double speed_of(unsigned lo, unsigned hi) {
+  if (hi & 0x80000000u) return from_words(lo, hi & 0x7fffffffu);
+  return from_words(~lo, ~hi);
+}
+
+// Values that a row holds for a system (NX: space dimensions; scalar laws in
+// either): r[0 .. n-1] of cell_speeds.
+template <int SYS, int NX>
+struct SpeedCount { enum { value = SYS == SYS_EULER ? (NX == 1 ? 3 : 6) : (SYS == SYS_BUCKLEY ? 2 : 4) }; };
+
+// Maxima of a wavefront's keys, wave-uniform.
+template <int NV>
+__device__ __forceinline__ void keys_max(unsigned long long (&k)[NV]) {
+  unsigned hi[NV], lo[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) hi[i] = (unsigned)(k[i] >> 32);
+  words_max<64, NV>(hi);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) lo[i] = (unsigned)(k[i] >> 32) == hi[i] ? (unsigned)k[i] : 0u;
+  words_max<64, NV>(lo);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) k[i] = ((unsigned long long)hi[i] << 32) | lo[i];
+}
+
+// Maxima over the block into row `dst`: atomically, or as the row's only
+// writer.  Every thread of the block calls.  (DPP maxima of the keys' words:
+// 0.4 us; 64-bit shuffles through LDS took 1.2 us.)
+template <int SYS, int NX, bool ATOMIC>
+__device__ __forceinline__ void block_speeds(const double (&r)[NPART], unsigned long long* __restrict__ dst) {
+  constexpr int NV = SpeedCount<SYS, NX>::value;
+  unsigned long long k[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) k[i] = speed_key(r[i]);
+  keys_max(k);
+  __shared__ unsigned long long sm[16][NV];
+  const int wv = wave_id();
+  if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) sm[wv][i] = k[i];
+  }
+  __syncthreads();
+  if (threadIdx.x < NV) {
+    unsigned long long v = sm[0][threadIdx.x];
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) v = sm[w][threadIdx.x] > v ? sm[w][threadIdx.x] : v;
+    if (ATOMIC) __hip_atomic_fetch_max(dst + threadIdx.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else dst[threadIdx.x] = v;
+  }
+}
+// The same of one wavefront.
+template <int SYS, int NX>
+__device__ __forceinline__ void wave_speeds_max(const double (&r)[NPART], unsigned long long* __restrict__ dst) {
+  constexpr int NV = SpeedCount<SYS, NX>::value;
+  unsigned long long k[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) k[i] = speed_key(r[i]);
+  keys_max(k);
+  const int lane = threadIdx.x & 63;
+  unsigned long long v = k[0];
+#pragma unroll
+  for (int i = 1; i < NV; ++i) v = lane == i ? k[i] : v;
+  if (lane < NV) __hip_atomic_fetch_max(dst + lane, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The inputs of stage_begin, loaded ahead of everything else a kernel loads
+// so that their latency hides behind those loads (2.4 us otherwise).
+template <int SYS, int NX>
+struct StageLoads {
+  enum { NV = SpeedCount<SYS, NX>::value, ROWS = SP_ROWS / 64 };
+  unsigned long long k[ROWS][NV];
+  DevCtl in;
+};
+template <int SYS, int NX>
+__device__ __forceinline__ void stage_load(const SweepArgs& a, StageLoads<SYS, NX>& L) {
+  typedef StageLoads<SYS, NX> S;
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int j = 0; j < S::ROWS; ++j) {
+    const int row = lane + 64 * j;
+#pragma unroll
+    for (int i = 0; i < S::NV; ++i) L.k[j][i] = row < a.sp_rows ? gptr(a.sp_in)[row * SP_STRIDE + i] : 0ull;
+  }
+  if (a.kind != FIN_RHS) L.in = *a.cin;
+}
+
+// The stage's constants from the rows of its input; false if the stage does
+// not run.  Every thread of the grid calls (bid: the block's index); block 0
+// stores the control block, all blocks together clear sp_zero.
+template <int SYS, int NX = 2>
+__device__ __forceinline__ bool stage_begin(const SweepArgs& a, const StageLoads<SYS, NX>& L, int bid, int dim,
+                                            SweepConst& kx, SweepConst& ky) {
+  constexpr int NV = SpeedCount<SYS, NX>::value;
+  unsigned long long best[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    best[i] = L.k[0][i];
+#pragma unroll
+    for (int j = 1; j < StageLoads<SYS, NX>::ROWS; ++j) best[i] = L.k[j][i] > best[i] ? L.k[j][i] : best[i];
+  }
+  keys_max(best);
+  double r[NPART];
+#pragma unroll
+  for (int i = 0; i < NPART; ++i) r[i] = i < NV ? speed_of((unsigned)best[i < NV ? i : 0], (unsigned)(best[i < NV ? i : 0] >> 32)) : 0.0;
+  const Phys& ph = a.ph;
+  const bool bad = !(r[0] < __builtin_huge_val());
+  double sx, sy;
+  if (SYS == SYS_BUCKLEY) {
+    sx = sy = bad ? 0.0 : buckley_max_speed(-r[1], r[0], ph.bl_root);
+    kx.al[0] = sx;
+    ky.al[0] = sy;
+  } else if (SYS == SYS_EULER) {
+    sx = wave_max(r[0], r[2]);
+    sy = wave_max(r[3], r[5]);
+    kx.al[0] = ph.lf_scalar ? sx : r[0];
+    kx.al[1] = kx.al[2] = ph.lf_scalar ? sx : r[1];
+    kx.al[3] = ph.lf_scalar ? sx : r[2];
+    ky.al[0] = ph.lf_scalar ? sy : r[3];
+    ky.al[1] = ky.al[2] = ph.lf_scalar ? sy : r[4];
+    ky.al[3] = ph.lf_scalar ? sy : r[5];
+  } else {
+    sx = r[0];
+    sy = r[3 < NV ? 3 : 0];
+    kx.al[0] = sx;
+    ky.al[0] = sy;
+  }
+  kx.smax = sx;
+  ky.smax = sy;
+  kx.mu = ky.mu = 0.0;
+  kx.dt = ky.dt = 0.0;
+  const bool leader = bid == 0 && threadIdx.x == 0;
+  if (a.kind == FIN_RHS) {
+    if (leader) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        if (SYS == SYS_EULER || s == 0) { a.ctl->alpha[0][s] = kx.al[s]; a.ctl->alpha[1][s] = ky.al[s]; }
+      }
+      if (bad) {
+        if (!a.ctl->bad) a.ctl->bad_step = a.ctl->steps;
+        a.ctl->bad = 1;
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if (SYS == SYS_EULER || s == 0) { kx.al[s] = scalar_of(kx.al[s]); ky.al[s] = scalar_of(ky.al[s]); }
+    }
+    return true;
+  }
+  const DevCtl& in = L.in;
+  bool run = in.active != 0;
+  double dt = in.dt, t = in.t;
+  int active = in.active, last = in.last, isbad = in.bad;
+  long long steps = in.steps, bad_step = in.bad_step;
+  double dt_min = in.dt_min, dt_max = in.dt_max;
+  if (run && bad) {
+    if (!isbad) bad_step = steps;
+    isbad = 1;
+    active = 0;
+    run = false;
+  }
+  if (run && a.kind == FIN_STAGE0) {
+    if ((in.max_steps > 0 && steps >= in.max_steps) || t >= in.t_final) {
+      active = 0;
+      run = false;
+    } else {
+      if (in.dt_fixed > 0.0) {
+        dt = in.dt_fixed;
+      } else if (ph.dt_rule == 1) {
+        const double h = dim == 2 ? fmin(a.g.dx, a.g.dy) : a.g.dx;
+        dt = ph.cfl * h * h;
+      } else if (dim == 1) {
+        dt = ph.cfl * a.g.dx / sx;
+      } else {
+        dt = ph.cfl / (sx / a.g.dx + sy / a.g.dy);
+      }
+      last = 0;
+      if (t + dt >= in.t_final) { dt = in.t_final - t; last = 1; }
+    }
+  }
+  if (run && a.kind == FIN_STAGE2) {   // the end of the step
+    t = last ? in.t_final : t + dt;
+    steps += 1;
+    dt_min = fmin(dt_min, dt);
+    dt_max = fmax(dt_max, dt);
+    if (last) active = 0;
+    if (in.max_steps > 0 && steps >= in.max_steps) active = 0;
+  }
+  if (leader) {
+    DevCtl* const o = a.ctl;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if (SYS == SYS_EULER || s == 0) { o->alpha[0][s] = kx.al[s]; o->alpha[1][s] = ky.al[s]; }
+    }
+    o->smax[0] = sx; o->smax[1] = sy;
+    o->dt = dt; o->t = t; o->t_final = in.t_final; o->dt_fixed = in.dt_fixed;
+    o->dt_min = dt_min; o->dt_max = dt_max;
+    o->steps = steps; o->max_steps = in.max_steps; o->bad_step = bad_step;
+    o->active = active; o->bad = isbad; o->last = last; o->run = run ? 1 : 0;
+    o->stuck = 0; o->line_tag = in.line_tag;
+  }
+  if (run) {
+    for (int i = bid * blockDim.x + threadIdx.x; i < SP_SET; i += a.nblk * blockDim.x) a.sp_zero[i] = 0;
+  }
+  // scalar registers, as if loaded from the control block
+  kx.dt = ky.dt = scalar_of(dt);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    if (SYS == SYS_EULER || s == 0) { kx.al[s] = scalar_of(kx.al[s]); ky.al[s] = scalar_of(ky.al[s]); }
+  }
+  if (ph.pp) {   // limiter step size mu = dt S / s_dir
+    const double S = fma(sx, a.g.inv_dx, dim == 2 ? sy * a.g.inv_dy : 0.0);
+    kx.mu = sx > 0.0 ? dt * S / sx : 0.0;
+    ky.mu = sy > 0.0 ? dt * S / sy : 0.0;
+  }
+  return run;
+}
+
 
 // ---------------------------------------------------------------------------
 // x-sweep: one wavefront per line segment of 64 interfaces / 63 cells.  The
@@ -487,9 +733,15 @@ __host__ __device__ constexpr int xs_rec(int R) { return (XS_CELLS + 2 * R + 7) 
 template <int SYS, int M, class T, int MODE, int WV, int R = 3, int PP = 0>
 __device__ __forceinline__ void sweep_x_body(const SweepArgs& a, const CfgArg<T>& cfg, int bid) {
   constexpr int XS_REC = xs_rec(R);
-  if (a.check_active && !gptr(a.ctl)->active) return;
-  const SweepConst sk = sweep_const<0>(a.ctl, a.g, PP && SYS == SYS_EULER && (MODE == MODE_LX || MODE == MODE_STAGE),
-                                       MODE == MODE_LX);
+  constexpr int NX = M == 3 ? 1 : 2;
+  SweepConst sk;
+  StageLoads<SYS, NX> sl;
+  if (a.sp_in) {
+    stage_load(a, sl);
+  } else {
+    if (a.check_run && !gptr(a.ctl)->run) return;
+    sk = sweep_const<0>(a.ctl, a.g, PP && SYS == SYS_EULER && (MODE == MODE_LX || MODE == MODE_STAGE), MODE == MODE_LX);
+  }
   constexpr int NF = NumFields<SYS, M>::value;
   __shared__ T xr[4][NF * XS_REC];
   __shared__ double fl[4][M][64];
@@ -503,18 +755,25 @@ __device__ __forceinline__ void sweep_x_body(const SweepArgs& a, const CfgArg<T>
   const int k = c0 + lane;
   const size_t cs = (size_t)nx * ny;
   const size_t row = (size_t)line * nx;
+  constexpr int NP = (XS_CELLS + 2 * R + 63) / 64;   // record passes
+  double qx[NP][M];
   if (live) {
-    constexpr int NX = (XS_CELLS + 2 * R + 63) / 64;   // record passes
-    double qx[NX][M];
 #pragma unroll
-    for (int t = 0; t < NX; ++t) {
+    for (int t = 0; t < NP; ++t) {
       const int idx = lane + 64 * t;
       if (idx < XS_CELLS + 2 * R)
         cell_load<SYS, M, 0>(a.q + row, cs, (size_t)bc_map_span(c0 - R + idx, c0 - R + 64 * t, 64, nx, a.g.bc_x),
                              qx[t]);
     }
+  }
+  if (a.sp_in) {
+    SweepConst ky;
+    if (!stage_begin(a, sl, bid, MODE == MODE_STAGE || M == 3 ? 1 : 2, sk, ky)) return;
+    if (!(PP && (MODE == MODE_LX || MODE == MODE_STAGE))) sk.mu = 0.0;
+  }
+  if (live) {
 #pragma unroll
-    for (int t = 0; t < NX; ++t) {
+    for (int t = 0; t < NP; ++t) {
       const int idx = lane + 64 * t;
       if (idx < XS_CELLS + 2 * R) cell_record<SYS, M, 0, T>(qx[t], a.ph, &xr[wv][idx], XS_REC);
     }
@@ -592,7 +851,9 @@ __device__ __forceinline__ void sweep_x_body(const SweepArgs& a, const CfgArg<T>
       if (MODE == MODE_STAGE) cell_speeds<SYS, M>(qnew, a.ph, rs);
     }
   }
-  if (MODE == MODE_STAGE && a.part) block_max_store(rs, a.part + (size_t)bid * NPART);
+  if (MODE == MODE_STAGE) {
+    block_speeds<SYS, NX, true>(rs, a.sp_out + (bid % SP_ROWS) * SP_STRIDE);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -640,25 +901,19 @@ __device__ __forceinline__ void xl_record(const double (&qp)[M], const Phys& ph,
   }
 }
 
-// The maxima of a wavefront's lanes to dst[0 .. NPART-1] (lane 0 stores).
-// cell_speeds leaves numbers or +inf, never NaN, so fmax is the exact max.
-__device__ __forceinline__ void wave_max_store(double (&r)[NPART], double* __restrict__ dst) {
-#pragma unroll
-  for (int i = 0; i < NPART; ++i) {
-    for (int off = 32; off > 0; off >>= 1) r[i] = fmax(r[i], __shfl_xor(r[i], off, 64));
-  }
-  if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-    for (int i = 0; i < NPART; ++i) gptr(dst)[i] = r[i];
-  }
-}
-
 template <int SYS, int M, int WV, int MODE = MODE_LX>
 __device__ __forceinline__ void sweep_xl_body(const SweepArgs& a, const CfgArg<double>& cfg, int bid) {
   static_assert(MODE == MODE_LX || MODE == MODE_STAGE, "the looped sweep writes stage states");
   constexpr int R = 3;
-  if (a.check_active && !gptr(a.ctl)->active) return;
-  const SweepConst sk = sweep_const<0>(a.ctl, a.g, false, MODE == MODE_LX);
+  constexpr int NX = M == 3 ? 1 : 2;
+  SweepConst sk;
+  StageLoads<SYS, NX> sl;
+  if (a.sp_in) {
+    stage_load(a, sl);
+  } else {
+    if (a.check_run && !gptr(a.ctl)->run) return;
+    sk = sweep_const<0>(a.ctl, a.g, false, MODE == MODE_LX);
+  }
   constexpr int NF = NumFields<SYS, M>::value;
   __shared__ double xr[4][NF * XL_RING];
   __shared__ double fl[4][M][66];   // [l + 1]: flux of lane l; [65]: carry from the previous chunk
@@ -670,7 +925,7 @@ __device__ __forceinline__ void sweep_xl_body(const SweepArgs& a, const CfgArg<d
   const int nseg = (nx + seg_cells - 1) / seg_cells;
   const int wid = bid * 4 + wv;
   const int line = wid / nseg, seg = wid - line * nseg;   // wave-uniform
-  if (line >= ny) return;   // the wavefronts of a block never wait for each other
+  const bool live = line < ny;   // (the others only take part in stage_begin)
   const int s0 = seg * seg_cells;
   const int nch = min(nc, (nx - s0) / 64 + 1);   // chunks holding interfaces <= nx
   const size_t cs = (size_t)nx * ny;
@@ -678,8 +933,6 @@ __device__ __forceinline__ void sweep_xl_body(const SweepArgs& a, const CfgArg<d
   double* const ring = &xr[wv][0];
   double(*const fw)[66] = fl[wv];
   const int bcx = a.g.bc_x;
-  // ca Q^n + cb Q - cb dt (F_{i+1/2} - F_{i-1/2}) / dx
-  const double kx = -(a.cb * sk.dt) * a.g.inv_dx;
   // ring slot of cell k is (k - s0 + R) mod 128; cells s0 - R .. s0 - R + 63 first
   double rs[NPART];
 #pragma unroll
@@ -687,11 +940,21 @@ __device__ __forceinline__ void sweep_xl_body(const SweepArgs& a, const CfgArg<d
   double qp[M];
   {
     double q0[M];   // both loads in flight before the first records
-    xl_load<SYS, M>(rowq, cs, bc_map(s0 - R + lane, nx, bcx), q0);
-    xl_load<SYS, M>(rowq, cs, bc_map(s0 - R + 64 + lane, nx, bcx), qp);
+    if (live) {
+      xl_load<SYS, M>(rowq, cs, bc_map(s0 - R + lane, nx, bcx), q0);
+      xl_load<SYS, M>(rowq, cs, bc_map(s0 - R + 64 + lane, nx, bcx), qp);
+    }
+    if (a.sp_in) {
+      SweepConst ky;
+      if (!stage_begin(a, sl, bid, MODE == MODE_STAGE ? 1 : 2, sk, ky)) return;
+      sk.mu = 0.0;
+    }
+    if (!live) return;   // the wavefronts of a block never wait for each other
     xl_record<SYS, M>(q0, a.ph, ring + lane);
     xl_record<SYS, M>(qp, a.ph, ring + xl_slot(64 + lane));
   }
+  // ca Q^n + cb Q - cb dt (F_{i+1/2} - F_{i-1/2}) / dx
+  const double kx = -(a.cb * sk.dt) * a.g.inv_dx;
   for (int j = 0; j < nch; ++j) {
     const int I0 = s0 + 64 * j;
     wave_sync();   // the records of cells I0 - R .. I0 + 124 - R are in the ring
@@ -753,7 +1016,9 @@ __device__ __forceinline__ void sweep_xl_body(const SweepArgs& a, const CfgArg<d
     // of cells I0 - R + lane, which this chunk was the last to read
     if (j + 1 < nch) xl_record<SYS, M>(qp, a.ph, ring + xl_slot(64 * j + 128 + lane));
   }
-  if (MODE == MODE_STAGE && a.part) wave_max_store(rs, a.part + (size_t)wid * NPART);
+  if (MODE == MODE_STAGE) {
+    wave_speeds_max<SYS, NX>(rs, a.sp_out + (wid % SP_ROWS) * SP_STRIDE);
+  }
 }
 
 template <int SYS, int M, int WV, int MODE = MODE_LX>
@@ -933,8 +1198,16 @@ __device__ __forceinline__ void sweep_y_tile(const SweepArgs& a, const CfgArg<T>
 // band by of the ceil(ny / ytile) bands of (near) equal height.
 template <int SYS, int M, class T, int MODE, int WV, int R = 3, int PP = 0>
 __device__ __forceinline__ void sweep_y_body(const SweepArgs& a, const CfgArg<T>& cfg, int bx, int by, int gx) {
-  if (a.check_active && !gptr(a.ctl)->active) return;
-  const SweepConst sk = sweep_const<1>(a.ctl, a.g, PP && SYS == SYS_EULER && MODE == MODE_STAGE, true);
+  SweepConst sk;
+  if (MODE != MODE_STAGE && a.sp_in) {   // a right-hand side or fluxes: no control block
+    SweepConst kx;
+    StageLoads<SYS, 2> sl;
+    stage_load(a, sl);
+    (void)stage_begin(a, sl, -1, 2, kx, sk);
+  } else {
+    if (a.check_run && !gptr(a.ctl)->run) return;
+    sk = sweep_const<1>(a.ctl, a.g, PP && SYS == SYS_EULER && MODE == MODE_STAGE, true);
+  }
   double rs[NPART];
 #pragma unroll
   for (int t = 0; t < NPART; ++t) rs[t] = -__builtin_huge_val();
@@ -942,8 +1215,9 @@ __device__ __forceinline__ void sweep_y_body(const SweepArgs& a, const CfgArg<T>
   const int nb = (ny + a.ytile - 1) / a.ytile;
   const int y0 = (int)((long long)by * ny / nb), ylast = (int)((long long)(by + 1) * ny / nb);
   sweep_y_tile<SYS, M, T, MODE, WV, R, PP>(a, cfg, sk, bx * 64 + wave_id() * YS_COLS, y0, ylast, rs);
-  if (MODE == MODE_STAGE && a.part)
-    block_max_store(rs, a.part + ((size_t)by * gx + bx) * NPART);
+  if (MODE == MODE_STAGE) {
+    block_speeds<SYS, 2, true>(rs, a.sp_out + ((by * gx + bx) % SP_ROWS) * SP_STRIDE);
+  }
 }
 
 // The fast variants (Z weights, p = 1, a stage or RHS mode) carry an
@@ -985,110 +1259,38 @@ __global__ __launch_bounds__(256, WAVES) void k_sweep_y_r(SweepArgs a, CfgArg<T>
 }
 
 
-__device__ __forceinline__ void step_end_body(DevCtl* ctl) {
-  if (threadIdx.x != 0 || !ctl->active) return;
-  const double dt = ctl->dt;
-  ctl->t = ctl->last ? ctl->t_final : ctl->t + dt;
-  ctl->steps += 1;
-  ctl->dt_min = fmin(ctl->dt_min, dt);
-  ctl->dt_max = fmax(ctl->dt_max, dt);
-  if (ctl->last) ctl->active = 0;
-  if (ctl->max_steps > 0 && ctl->steps >= ctl->max_steps) ctl->active = 0;
+// stage_begin as a launch of its own (one wavefront), ahead of sweeps of so
+// many blocks that each block's share of it would cost more.
+template <int SYS, int NX>
+__global__ __launch_bounds__(64) void k_stage_begin(SweepArgs a, int dim) {
+  SweepConst kx, ky;
+  StageLoads<SYS, NX> sl;
+  stage_load(a, sl);
+  (void)stage_begin(a, sl, 0, dim, kx, ky);
 }
 
-// FIN_END_STAGE0: the previous step's end (step_end_body), then FIN_STAGE0,
-// in one launch.
-enum FinalKind { FIN_RHS = 0, FIN_STAGE0 = 1, FIN_STAGEK = 2, FIN_END_STAGE0 = 3 };
-
-__device__ __forceinline__ void wave_final_body(const double* __restrict__ part, int nblk, DevCtl* ctl,
-                                                const Geom& g, const Phys& ph, int dim, int kind, int sys) {
-  // every thread of the block (one or more wavefronts) folds a strided share
-  // of the per-block maxima; the maxima are exact whatever the order
+// Stand-alone wave-speed pass of at most SP_ROWS blocks: row b of the first
+// set from block b's share of the cells.  clear: also clear the set's other
+// rows and the other sets, and (ctl) start a stepping sequence from v.
+template <int SYS, int M>
+__global__ __launch_bounds__(1024) void k_speed_rows(const double* __restrict__ q, size_t ncell, Phys ph,
+                                                     unsigned long long* __restrict__ rows, int clear, DevCtl* ctl,
+                                                     DevCtl v) {
+  if (blockIdx.x == 0 && clear) {
+    if (ctl && threadIdx.x == 0) *ctl = v;
+    for (int i = gridDim.x * SP_STRIDE + threadIdx.x; i < SP_SETS * SP_SET; i += blockDim.x) rows[i] = 0;
+  }
   double r[NPART];
 #pragma unroll
   for (int i = 0; i < NPART; ++i) r[i] = -__builtin_huge_val();
-#pragma unroll 2
-  for (int b = threadIdx.x; b < nblk; b += blockDim.x) {
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < ncell; i += (size_t)gridDim.x * blockDim.x) {
+    double Q[M];
 #pragma unroll
-    for (int i = 0; i < NPART; ++i) r[i] = wave_max(r[i], part[(size_t)b * NPART + i]);
+    for (int c = 0; c < M; ++c) Q[c] = gptr(q)[c * ncell + i];
+    cell_speeds<SYS, M>(Q, ph, r);
   }
-#pragma unroll
-  for (int i = 0; i < NPART; ++i) {
-    for (int off = 32; off > 0; off >>= 1) r[i] = wave_max(r[i], __shfl_xor(r[i], off, 64));
-  }
-  if (blockDim.x > 64) {
-    __shared__ double red[16][NPART];
-    if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-      for (int i = 0; i < NPART; ++i) red[threadIdx.x >> 6][i] = r[i];
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
-#pragma unroll
-        for (int i = 0; i < NPART; ++i) r[i] = wave_max(r[i], red[w][i]);
-      }
-    }
-  }
-  if (threadIdx.x != 0) return;
-  if (kind == FIN_END_STAGE0) {
-    step_end_body(ctl);
-    kind = FIN_STAGE0;
-  }
-  if (kind != FIN_RHS && !ctl->active) return;
-  const bool bad = !(r[0] < __builtin_huge_val());
-  double sx = wave_max(r[0], r[2]), sy = wave_max(r[3], r[5]);
-  if (sys == SYS_BUCKLEY) {
-    sx = sy = bad ? 0.0 : buckley_max_speed(-r[1], r[0], ph.bl_root);
-    ctl->alpha[0][0] = sx;
-    ctl->alpha[1][0] = sy;
-  } else if (sys == SYS_EULER) {
-    if (ph.lf_scalar) {
-      for (int s = 0; s < 4; ++s) { ctl->alpha[0][s] = sx; ctl->alpha[1][s] = sy; }
-    } else {
-      ctl->alpha[0][0] = r[0]; ctl->alpha[0][1] = r[1]; ctl->alpha[0][2] = r[1]; ctl->alpha[0][3] = r[2];
-      ctl->alpha[1][0] = r[3]; ctl->alpha[1][1] = r[4]; ctl->alpha[1][2] = r[4]; ctl->alpha[1][3] = r[5];
-    }
-  } else {
-    ctl->alpha[0][0] = r[0];
-    ctl->alpha[1][0] = r[3];
-  }
-  ctl->smax[0] = sx;
-  ctl->smax[1] = sy;
-  if (bad) {
-    if (!ctl->bad) ctl->bad_step = ctl->steps;
-    ctl->bad = 1;
-    if (kind != FIN_RHS) ctl->active = 0;
-    return;
-  }
-  if (kind == FIN_STAGE0) {
-    if (ctl->max_steps > 0 && ctl->steps >= ctl->max_steps) { ctl->active = 0; return; }
-    if (ctl->t >= ctl->t_final) { ctl->active = 0; return; }
-    double dt;
-    if (ctl->dt_fixed > 0.0) {
-      dt = ctl->dt_fixed;
-    } else if (ph.dt_rule == 1) {
-      const double h = dim == 2 ? fmin(g.dx, g.dy) : g.dx;
-      dt = ph.cfl * h * h;
-    } else if (dim == 1) {
-      dt = ph.cfl * g.dx / sx;
-    } else {
-      dt = ph.cfl / (sx / g.dx + sy / g.dy);
-    }
-    ctl->last = 0;
-    if (ctl->t + dt >= ctl->t_final) { dt = ctl->t_final - ctl->t; ctl->last = 1; }
-    ctl->dt = dt;
-  }
+  block_speeds<SYS, M == 3 ? 1 : 2, false>(r, rows + (size_t)blockIdx.x * SP_STRIDE);
 }
-
-template <int M>
-__global__ __launch_bounds__(256) void k_wave_final(const double* __restrict__ part, int nblk, DevCtl* ctl,
-                                                   Geom g, Phys ph, int dim, int kind, int sys) {
-  wave_final_body(part, nblk, ctl, g, ph, dim, kind, sys);
-}
-
-
-static __global__ void k_step_end(DevCtl* ctl) { step_end_body(ctl); }
 
 // Fixed-order FP64 sums of each component (deterministic for a given size):
 // block b sums the contiguous chunk [b*chunk, (b+1)*chunk) with a fixed tree.

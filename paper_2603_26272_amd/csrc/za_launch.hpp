@@ -7,45 +7,55 @@
 
 namespace za {
 
+// 2D Euler stages and right-hand sides are fused (za_fused.hpp): of the
+// separate sweeps there remain the flux output and the limited stages.
 template <int SYS, int M, class T, int WV>
-static void launch_x_t(za_ctx* c, int mode, const SweepArgs& a) {
+static void launch_x_t(za_ctx* c, int mode, SweepArgs a) {
   const CfgArg<T> cfg = make_cfg<T>(c->prob);
   const int nseg = (a.g.nx + XS_CELLS - 1) / XS_CELLS;
   const long long waves = (long long)a.g.ny * nseg;
   const dim3 grid((unsigned)((waves + 3) / 4)), blk(256);
+  a.nblk = (int)grid.x;
   if constexpr (SYS == SYS_EULER && sizeof(T) == sizeof(double)) {
-    if (c->ph.pp && (mode == MODE_LX || mode == MODE_STAGE)) {
-      if (mode == MODE_LX)
-        hipLaunchKernelGGL((k_sweep_x_pp<M, MODE_LX, WV>), grid, blk, 0, c->stream, a, cfg);
-      else
-        hipLaunchKernelGGL((k_sweep_x_pp<M, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg);
+    if (c->ph.pp && mode == (M == 3 ? MODE_STAGE : MODE_LX)) {
+      hipLaunchKernelGGL((k_sweep_x_pp<M, (M == 3 ? MODE_STAGE : MODE_LX), WV>), grid, blk, 0, c->stream, a, cfg);
       return;
     }
   }
-  if constexpr (sizeof(T) == sizeof(double) && WV == WV_Z1) {
-    if ((mode == MODE_LX || mode == MODE_STAGE) && a.xl_chunks > 0) {
-      const long long w = xl_waves(a.g.nx, a.g.ny, a.xl_chunks);
-      const dim3 gl((unsigned)((w + 3) / 4));
-      if (mode == MODE_LX)
-        hipLaunchKernelGGL((k_sweep_xl<SYS, M, WV, MODE_LX>), gl, blk, 0, c->stream, a, cfg);
-      else
+  if (mode == MODE_FLUX) {
+    hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg);
+    return;
+  }
+  if constexpr (M != 4) {
+    if constexpr (sizeof(T) == sizeof(double) && WV == WV_Z1) {
+      if ((mode == MODE_LX || mode == MODE_STAGE) && a.xl_chunks > 0) {
+        const long long w = xl_waves(a.g.nx, a.g.ny, a.xl_chunks);
+        const dim3 gl((unsigned)((w + 3) / 4));
+        a.nblk = (int)gl.x;
+        if constexpr (SYS != SYS_EULER) {
+          if (mode == MODE_LX) {
+            hipLaunchKernelGGL((k_sweep_xl<SYS, M, WV, MODE_LX>), gl, blk, 0, c->stream, a, cfg);
+            return;
+          }
+        }
         hipLaunchKernelGGL((k_sweep_xl<SYS, M, WV, MODE_STAGE>), gl, blk, 0, c->stream, a, cfg);
-      return;
+        return;
+      }
     }
-  }
-  if constexpr (WV == WV_Z1) {
-    switch (mode) {
-      case MODE_FLUX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      case MODE_RHS: hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      case MODE_LX: hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_LX, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      default: hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg); break;
-    }
-  } else {
-    switch (mode) {
-      case MODE_FLUX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      case MODE_RHS: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      case MODE_LX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_LX, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      default: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg); break;
+    if constexpr (WV == WV_Z1) {
+      if (mode == MODE_RHS)
+        hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg);
+      else if (mode == MODE_STAGE)
+        hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg);
+      else if constexpr (SYS != SYS_EULER)
+        hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_LX, WV>), grid, blk, 0, c->stream, a, cfg);
+    } else {
+      if (mode == MODE_RHS)
+        hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg);
+      else if (mode == MODE_STAGE)
+        hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg);
+      else if constexpr (SYS != SYS_EULER)
+        hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_LX, WV>), grid, blk, 0, c->stream, a, cfg);
     }
   }
 }
@@ -54,24 +64,25 @@ template <int SYS, int M, class T, int WV>
 static void launch_y_t(za_ctx* c, int mode, const SweepArgs& a) {
   const CfgArg<T> cfg = make_cfg<T>(c->prob);
   const dim3 grid((unsigned)((a.g.nx + 63) / 64), (unsigned)((a.g.ny + a.ytile - 1) / a.ytile)), blk(256);
-  if constexpr (SYS == SYS_EULER && M == 4 && sizeof(T) == sizeof(double)) {
-    if (c->ph.pp && mode == MODE_STAGE) {
-      hipLaunchKernelGGL((k_sweep_y_pp<MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg);
-      return;
-    }
+  if (mode == MODE_FLUX) {
+    hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg);
+    return;
   }
-  if constexpr (WV == WV_Z1) {
-    switch (mode) {
-      case MODE_FLUX: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      case MODE_RHS: hipLaunchKernelGGL((k_sweep_y<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      default: hipLaunchKernelGGL((k_sweep_y<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg); break;
+  if constexpr (SYS == SYS_EULER) {
+    if constexpr (sizeof(T) == sizeof(double)) {
+      if (mode == MODE_STAGE)   // limited
+        hipLaunchKernelGGL((k_sweep_y_pp<MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg);
     }
+  } else if constexpr (WV == WV_Z1) {
+    if (mode == MODE_RHS)
+      hipLaunchKernelGGL((k_sweep_y<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg);
+    else
+      hipLaunchKernelGGL((k_sweep_y<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg);
   } else {
-    switch (mode) {
-      case MODE_FLUX: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      case MODE_RHS: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg); break;
-      default: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg); break;
-    }
+    if (mode == MODE_RHS)
+      hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg);
+    else
+      hipLaunchKernelGGL((k_sweep_y_any<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg);
   }
 }
 
@@ -104,7 +115,7 @@ void launch_y_wv(za_ctx* c, int mode, const SweepArgs& a) {
 }
 
 // Resident blocks per CU of the y-sweep that a stage of p launches (for the
-// band height); 0 if unknown.
+// band height; Euler: the limited one); 0 if unknown.
 template <int WV>
 int y_blocks_per_cu_wv(const za_problem& p) {
   const void* fn;
@@ -116,17 +127,8 @@ int y_blocks_per_cu_wv(const za_problem& p) {
       fn = p.precision == ZA_FP32_RECON
                ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_ADV, 1, float, MODE_STAGE, WV>)
                : reinterpret_cast<const void*>(&k_sweep_y_any<SYS_ADV, 1, double, MODE_STAGE, WV>);
-  } else if (p.pp_limiter) {
-    fn = reinterpret_cast<const void*>(&k_sweep_y_pp<MODE_STAGE, WV>);
   } else {
-    if constexpr (WV == WV_Z1)
-      fn = p.precision == ZA_FP32_RECON
-               ? reinterpret_cast<const void*>(&k_sweep_y<SYS_EULER, 4, float, MODE_STAGE, WV>)
-               : reinterpret_cast<const void*>(&k_sweep_y<SYS_EULER, 4, double, MODE_STAGE, WV>);
-    else
-      fn = p.precision == ZA_FP32_RECON
-               ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_EULER, 4, float, MODE_STAGE, WV>)
-               : reinterpret_cast<const void*>(&k_sweep_y_any<SYS_EULER, 4, double, MODE_STAGE, WV>);
+    fn = reinterpret_cast<const void*>(&k_sweep_y_pp<MODE_STAGE, WV>);
   }
   int n = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, 256, 0) != hipSuccess) return 0;

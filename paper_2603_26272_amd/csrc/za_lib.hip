@@ -92,16 +92,18 @@ size_t za_state_count(const za_problem* p) {
   return (size_t)ncomp_of(*p) * p->nx * p->ny;
 }
 
+// device bytes of the partial sums, and of the rows and control blocks
+static constexpr int SUM_BLOCKS = 6144;
+static constexpr size_t kPartBytes = (size_t)SUM_BLOCKS * sizeof(double);
+static constexpr size_t kRowsBytes = SP_SETS * SP_SET * sizeof(unsigned long long) + 1024;
+static_assert(CTL_COPIES * sizeof(DevCtl) <= 1024, "the control blocks");
+
 size_t za_workspace_bytes(const za_problem* p) {
   if (za_validate(p, nullptr) != ZA_OK) return 0;
   const size_t st = za_state_count(p) * sizeof(double);
   size_t b = 2 * st;                      // Q1, Q2
-  if (p->dim == 2) b += st;               // L_x
-  // reduction partials: at most one per stage-kernel block (bounded by the
-  // grid), at least RED_BLOCKS_MAX
-  const size_t blocks = p->dim == 2 ? (size_t)((p->nx + 63) / 64) * (size_t)((p->ny + 15) / 16)
-                                    : (size_t)(((p->nx + XS_CELLS - 1) / XS_CELLS + 3) / 4);
-  b += std::max<size_t>(RED_BLOCKS_MAX, blocks) * NPART * sizeof(double) + 4096 + sizeof(DevCtl);
+  if (p->dim == 2) b += st;               // the partial stage (counted for fused stages too)
+  b += kPartBytes + kRowsBytes;            // partial sums, wave-speed rows, control blocks
   int lb, lw;
   line_shape(*p, &lb, &lw);
   b += line_bytes(lb);                    // exchange words of the resident 1D kernel
@@ -172,34 +174,27 @@ void launch_y(za_ctx* c, int mode, const SweepArgs& a) {
   timed_end(c, 1);
 }
 
-static void launch_final(za_ctx* c, int kind, int nblk) {
-  hipLaunchKernelGGL((k_wave_final<4>), dim3(1), dim3(256), 0, c->stream, c->part, nblk, c->ctl, c->geom, c->ph,
-                     c->prob.dim, kind, (int)c->prob.system);
-}
-
-// Stand-alone wave-speed reduction of q followed by the final reduction.
-void launch_wave(za_ctx* c, const double* q, int kind, int check_active) {
+// Stand-alone wave-speed pass over q, for steps (clear; start: which begin a
+// stepping sequence from this control block) or a right-hand side.
+void launch_speeds(za_ctx* c, const double* q, int clear, const DevCtl* start) {
   timed_begin(c, 2);
   const size_t ncell = (size_t)c->prob.nx * c->prob.ny;
-  const int nblk = c->red_blocks;
+  DevCtl v;
+  std::memset(&v, 0, sizeof(v));
+  if (start) v = *start;
+  const dim3 grid(c->red_blocks), blk(c->red_threads);
+  DevCtl* const ctl = start ? c->ctl : nullptr;
+#define ZA_S(SYS, M) \
+  hipLaunchKernelGGL((k_speed_rows<SYS, M>), grid, blk, 0, c->stream, q, ncell, c->ph, c->rows, clear, ctl, v)
   switch (c->prob.system) {
     case ZA_EULER:
-      if (c->prob.dim == 1)
-        hipLaunchKernelGGL((k_wave_partial<SYS_EULER, 3>), dim3(nblk), dim3(256), 0, c->stream, q, ncell, c->ph, c->ctl, check_active, c->part);
-      else
-        hipLaunchKernelGGL((k_wave_partial<SYS_EULER, 4>), dim3(nblk), dim3(256), 0, c->stream, q, ncell, c->ph, c->ctl, check_active, c->part);
+      if (c->prob.dim == 1) ZA_S(SYS_EULER, 3); else ZA_S(SYS_EULER, 4);
       break;
-    case ZA_ADVECTION:
-      hipLaunchKernelGGL((k_wave_partial<SYS_ADV, 1>), dim3(nblk), dim3(256), 0, c->stream, q, ncell, c->ph, c->ctl, check_active, c->part);
-      break;
-    case ZA_BURGERS:
-      hipLaunchKernelGGL((k_wave_partial<SYS_BURGERS, 1>), dim3(nblk), dim3(256), 0, c->stream, q, ncell, c->ph, c->ctl, check_active, c->part);
-      break;
-    default:
-      hipLaunchKernelGGL((k_wave_partial<SYS_BUCKLEY, 1>), dim3(nblk), dim3(256), 0, c->stream, q, ncell, c->ph, c->ctl, check_active, c->part);
-      break;
+    case ZA_ADVECTION: ZA_S(SYS_ADV, 1); break;
+    case ZA_BURGERS: ZA_S(SYS_BURGERS, 1); break;
+    default: ZA_S(SYS_BUCKLEY, 1); break;
   }
-  launch_final(c, kind, nblk);
+#undef ZA_S
   timed_end(c, 2);
 }
 
@@ -222,7 +217,6 @@ SweepArgs base_args(za_ctx* c) {
   a.g = c->geom;
   a.ph = c->ph;
   a.ytile = c->ytile;
-  a.part = nullptr;
   a.xl_chunks = c->xl_chunks;
   return a;
 }
@@ -234,7 +228,8 @@ static int pick_ytile(za_ctx* c) {
   const za_problem& p = c->prob;
   if (p.dim != 2) return 64;
   int cus = 0;
-  int blocks_per_cu = order_of(p) != 3      ? order_y_blocks_per_cu(p)
+  int blocks_per_cu = c->fu_gx && !p.pp_limiter ? 3   // (flux output only)
+                      : order_of(p) != 3    ? order_y_blocks_per_cu(p)
                       : !general_weights(p) ? y_blocks_per_cu_wv<WV_Z1>(p)
                       : square_powers(p)    ? square_y_blocks_per_cu(p)
                                             : general_y_blocks_per_cu(p);
@@ -259,14 +254,13 @@ static int pick_ytile(za_ctx* c) {
 // ZA_XL_CHUNKS in the environment forces a value (0 disables the sweep).
 static int pick_xl_chunks(za_ctx* c) {
   const za_problem& p = c->prob;
-  if (p.precision != ZA_FP64 || order_of(p) != 3 || p.pp_limiter || general_weights(p)) return 0;
+  if (p.precision != ZA_FP64 || order_of(p) != 3 || p.pp_limiter || general_weights(p) || c->fu_gx) return 0;
   if (const char* e = std::getenv("ZA_XL_CHUNKS")) {
     const int v = std::atoi(e);
     return v < 0 ? 0 : std::min(v, 256);
   }
   int blocks_per_cu = 0, cus = 0;
   const void* fn = p.system != ZA_EULER ? reinterpret_cast<const void*>(&k_sweep_xl<SYS_ADV, 1, WV_Z1, MODE_LX>)
-                   : p.dim == 2         ? reinterpret_cast<const void*>(&k_sweep_xl<SYS_EULER, 4, WV_Z1, MODE_LX>)
                                         : reinterpret_cast<const void*>(&k_sweep_xl<SYS_EULER, 3, WV_Z1, MODE_STAGE>);
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks_per_cu, fn, 256, 0) != hipSuccess || blocks_per_cu < 1)
     blocks_per_cu = 3;
@@ -285,61 +279,99 @@ static int pick_xl_chunks(za_ctx* c) {
   return best;
 }
 
-// One RK3 step on the stream (no host synchronisation).  The kernel that
-// writes a stage's new state also leaves the per-block wave-speed maxima of
-// that state in c->part, so only the first step of an API call needs a
-// stand-alone reduction pass.
-// merge_end: the previous step deferred its end to this step's first final
-// reduction; defer_end: leave this step's end to the next step.
-static za_status enqueue_step(za_ctx* c, double* q, bool merge_end = false, bool defer_end = false) {
+// Sweeps of more blocks than this take their constants from a stage_begin
+// launch (5 us) instead of each block's own (1 us, of which two rounds of
+// resident blocks hide most): a 2048^2 right-hand side by one-shot sweeps of
+// 16,900 blocks took 297 us with the one and 271 us with the other.
+static constexpr long long kBeginBlocks = 3072;
+
+// Whether the first sweep of a stage (mode) has that many blocks; then the
+// launch, after which the sweeps read a.ctl.
+static bool begin_apart(za_ctx* c, int mode, SweepArgs& a) {
+  const long long nseg = (c->prob.nx + XS_CELLS - 1) / XS_CELLS;
+  const bool looped = c->xl_chunks > 0 && (mode == MODE_LX || mode == MODE_STAGE);
+  const long long waves = looped ? xl_waves(c->prob.nx, c->prob.ny, c->xl_chunks) : nseg * c->prob.ny;
+  if (waves / 4 <= kBeginBlocks) return false;
+  const dim3 one(1), blk(64);
+  a.nblk = 1;
+  switch (c->prob.system) {
+    case ZA_EULER:
+      if (c->prob.dim == 1) hipLaunchKernelGGL((k_stage_begin<SYS_EULER, 1>), one, blk, 0, c->stream, a, 1);
+      else hipLaunchKernelGGL((k_stage_begin<SYS_EULER, 2>), one, blk, 0, c->stream, a, 2);
+      break;
+    case ZA_ADVECTION: hipLaunchKernelGGL((k_stage_begin<SYS_ADV, 2>), one, blk, 0, c->stream, a, c->prob.dim); break;
+    case ZA_BURGERS: hipLaunchKernelGGL((k_stage_begin<SYS_BURGERS, 2>), one, blk, 0, c->stream, a, c->prob.dim); break;
+    default: hipLaunchKernelGGL((k_stage_begin<SYS_BUCKLEY, 2>), one, blk, 0, c->stream, a, c->prob.dim); break;
+  }
+  a.sp_in = nullptr;
+  a.check_run = a.kind != FIN_RHS;
+  return true;
+}
+
+// One RK3 step on the stream (no host synchronisation): per stage one fused
+// kernel, one 1D sweep, or an x-sweep and a y-sweep.  The kernel that writes
+// a stage's new state also leaves the wave-speed maxima of that state, and the
+// first kernel of a stage turns the maxima of its input into the stage's
+// constants (stage_begin), so only the first step of an API call needs a
+// stand-alone pass.  start: begin a stepping sequence from this control block
+// (with the stand-alone pass).
+static za_status enqueue_step(za_ctx* c, double* q, const DevCtl* start = nullptr) {
   const double ca[3] = {0.0, 0.75, 1.0 / 3.0};
   const double cb[3] = {1.0, 0.25, 2.0 / 3.0};
+  const int kind[3] = {FIN_STAGE0, FIN_STAGEK, FIN_STAGE2};
   const double* in[3] = {q, c->q1, c->q2};
   double* out[3] = {c->q1, c->q2, q};
   for (int s = 0; s < 3; ++s) {
-    const int kind = s == 0 ? FIN_STAGE0 : FIN_STAGEK;
-    if (s == 0 && !c->speeds_valid) {
-      if (merge_end) hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, c->stream, c->ctl);
-      launch_wave(c, in[s], kind, 1);
-    } else {
-      launch_final(c, s == 0 && merge_end ? FIN_END_STAGE0 : kind, c->stage_blocks);
-    }
+    if (s == 0 && !c->speeds_valid) launch_speeds(c, q, 1, start);
     SweepArgs a = base_args(c);
-    a.check_active = 1;
     a.q = in[s];
     a.qn = q;
     a.ca = ca[s];
     a.cb = cb[s];
-    a.part = c->part;
+    a.kind = kind[s];
+    a.cin = c->ctl + s;
+    a.ctl = c->ctl + (s + 1) % 3;
+    a.sp_in = c->rows + s * SP_SET;
+    a.sp_rows = SP_ROWS;
+    a.sp_out = c->rows + (s + 1) % 3 * SP_SET;
+    a.sp_zero = c->rows + (s + 2) % 3 * SP_SET;
+    a.out = out[s];
     if (c->prob.dim == 1) {
-      a.out = out[s];
+      begin_apart(c, MODE_STAGE, a);
       launch_x(c, MODE_STAGE, a);
+    } else if (c->fu_gx && !c->ph.pp) {
+      timed_begin(c, 1);
+      launch_fused(c, MODE_STAGE, a);
+      timed_end(c, 1);
     } else {
       a.out = c->lx;
+      begin_apart(c, MODE_LX, a);
       launch_x(c, MODE_LX, a);
+      a.sp_in = nullptr;     // the x-sweep has left the stage's constants in ctl
+      a.check_run = 1;
       a.lx = c->lx;
       a.out = out[s];
       launch_y(c, MODE_STAGE, a);
     }
   }
-  if (!defer_end) hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, c->stream, c->ctl);
   c->speeds_valid = true;
   ZA_CHECK_LAUNCH(c, "step launch");
   return ZA_OK;
 }
 
-// n RK3 steps.  After the first step of an API call (which may need the
-// stand-alone wave-speed pass), runs of GRAPH_STEPS steps replay a hipGraph
-// captured once per state pointer on a private capture stream; kernels read
-// dt and the LF speeds from the device control block, so a graph is valid
-// for any step.  Kernel timing (events) uses direct launches.
+// n RK3 steps (start: as for enqueue_step).  After the first step of an API
+// call (which needs the stand-alone wave-speed pass), runs of GRAPH_STEPS
+// steps replay a hipGraph captured once per state pointer on a private
+// capture stream; kernels read dt and the LF speeds from the device control
+// block, so a graph is valid for any step.  Kernel timing (events) uses
+// direct launches.
 static constexpr int GRAPH_STEPS = 16;
 
-static za_status enqueue_steps(za_ctx* c, double* q, int64_t n) {
+static za_status enqueue_steps(za_ctx* c, double* q, int64_t n, const DevCtl* start) {
   za_status st;
   int64_t done = 0;
   if (n > 0 && !c->speeds_valid) {
-    if ((st = enqueue_step(c, q)) != ZA_OK) return st;
+    if ((st = enqueue_step(c, q, start)) != ZA_OK) return st;
     done = 1;
   }
   if (!c->timing && c->graphs_ok && n - done >= GRAPH_STEPS) {
@@ -351,10 +383,7 @@ static za_status enqueue_steps(za_ctx* c, double* q, int64_t n) {
         c->stream = c->capture_stream;
         hipGraph_t g = nullptr;
         bool ok = hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
-        // inside the graph each step's end runs with the next step's first
-        // final reduction; the graph's last step ends on its own
-        for (int i = 0; ok && i < GRAPH_STEPS; ++i)
-          ok = enqueue_step(c, q, i > 0, i + 1 < GRAPH_STEPS) == ZA_OK;
+        for (int i = 0; ok && i < GRAPH_STEPS; ++i) ok = enqueue_step(c, q) == ZA_OK;
         ok = (hipStreamEndCapture(c->stream, &g) == hipSuccess) && ok;
         c->stream = user;
         if (ok) ok = hipGraphInstantiate(&c->graph_exec, g, nullptr, nullptr, 0) == hipSuccess;
@@ -374,10 +403,8 @@ static za_status enqueue_steps(za_ctx* c, double* q, int64_t n) {
       done += GRAPH_STEPS;
     }
   }
-  for (bool pending = false; done < n; ++done) {
-    const bool defer = done + 1 < n;
-    if ((st = enqueue_step(c, q, pending, defer)) != ZA_OK) return st;
-    pending = defer;
+  for (; done < n; ++done) {
+    if ((st = enqueue_step(c, q)) != ZA_OK) return st;
   }
   return ZA_OK;
 }
@@ -407,7 +434,6 @@ static DevCtl start_ctl(double dt_fixed, double t_final, int64_t max_steps) {
 static void launch_ctl(za_ctx* c, const DevCtl& v) {
   hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, c->stream, c->ctl, v);
 }
-void launch_ctl_reset(za_ctx* c) { launch_ctl(c, fresh_ctl()); }
 
 // The control block after everything enqueued so far (waits for it).
 static za_status read_ctl(za_ctx* c, DevCtl* h) {
@@ -433,17 +459,19 @@ static za_status advance(za_ctx* c, double* q, int64_t n, const DevCtl* start, b
     ZA_CHECK_LAUNCH(c, "step launch");
     return read ? read_ctl(c, h) : ZA_OK;
   }
-  const DevCtl before = start ? *start : *h;
-  if (start) launch_ctl(c, *start);
   if (line_ready(c)) {
+    const DevCtl before = start ? *start : *h;
+    if (start) launch_ctl(c, *start);
     launch_line(c, q, n, nullptr);
     ZA_CHECK_LAUNCH(c, "step launch");
     if ((st = read_ctl(c, h)) != ZA_OK) return st;
     if (!h->stuck) return ZA_OK;
     c->line_ok = false;
-    launch_ctl(c, before);
+    c->speeds_valid = false;
+    if ((st = enqueue_steps(c, q, n, &before)) != ZA_OK) return st;
+  } else if ((st = enqueue_steps(c, q, n, start)) != ZA_OK) {
+    return st;
   }
-  if ((st = enqueue_steps(c, q, n)) != ZA_OK) return st;
   return read ? read_ctl(c, h) : ZA_OK;
 }
 
@@ -472,18 +500,12 @@ void init_shape(za_ctx* c, const za_problem* p, hipStream_t stream) {
   c->ph.lf_scalar = p->lf == ZA_LF_SCALAR ? 1 : 0;
   c->ph.pp = p->pp_limiter ? 1 : 0;
   buckley_roots(c->ph.bl_root);
-  c->red_blocks = (int)std::min<size_t>(RED_BLOCKS_MAX, std::max<size_t>(1, (ncell + 2047) / 2048));
+  // stand-alone wave-speed pass: at most one block per CU
+  c->red_threads = ncell <= 65536 ? 256 : 1024;
+  c->red_blocks = (int)std::min<size_t>(SP_ROWS, (ncell + c->red_threads - 1) / c->red_threads);
+  fused_shape(*p, &c->fu_gx, &c->fu_gy);
   c->ytile = pick_ytile(c);
   c->xl_chunks = pick_xl_chunks(c);
-  if (p->dim == 2) {
-    c->stage_blocks = ((p->nx + 63) / 64) * ((p->ny + c->ytile - 1) / c->ytile);
-  } else if (c->xl_chunks > 0) {   // one row of maxima per wavefront of the looped sweep
-    c->stage_blocks = (int)xl_waves(p->nx, p->ny, c->xl_chunks);
-  } else {
-    const long long nseg = (p->nx + XS_CELLS - 1) / XS_CELLS;
-    c->stage_blocks = (int)((nseg * p->ny + 3) / 4);
-  }
-  c->part_blocks = std::max(RED_BLOCKS_MAX, c->stage_blocks);
   // ZA_STEP_GRAPHS=0 runs the steps of za_solve as direct launches instead
   // of replaying captured step graphs (results are identical)
   if (const char* e = std::getenv("ZA_STEP_GRAPHS")) c->graphs_ok = std::atoi(e) != 0;
@@ -496,10 +518,48 @@ void init_shape(za_ctx* c, const za_problem* p, hipStream_t stream) {
   if ((e = std::getenv("ZA_LINE_SPIN"))) c->line_spin = std::atoll(e);
 }
 
+// A right-hand side or flux sweep of q, whose speeds are in c->rows.
+SweepArgs rhs_args(za_ctx* c, const double* q, double* out) {
+  SweepArgs a = base_args(c);
+  a.q = q;
+  a.out = out;
+  a.kind = FIN_RHS;
+  a.sp_in = c->rows;
+  a.sp_rows = c->red_blocks;
+  return a;
+}
+
+// rhs = L(q): one launch where one block holds the line, else the wave-speed
+// pass and a fused kernel, a 1D sweep or a pair of sweeps.
+void launch_rhs(za_ctx* c, const double* q, double* rhs) {
+  if (line_ready(c) && c->line_blocks == 1) {
+    launch_line_rhs(c, q, rhs);
+    return;
+  }
+  launch_speeds(c, q, 0, nullptr);
+  SweepArgs a = rhs_args(c, q, rhs);
+  if (c->fu_gx) {
+    timed_begin(c, 1);
+    launch_fused(c, MODE_RHS, a);
+    timed_end(c, 1);
+    return;
+  }
+  begin_apart(c, MODE_RHS, a);
+  launch_x(c, MODE_RHS, a);
+  if (c->prob.dim == 2) {
+    a.lx = rhs;
+    launch_y(c, MODE_RHS, a);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // C ABI
 // ---------------------------------------------------------------------------
 extern "C" {
+
+// Whether stages are pairs of sweeps with a partial stage between them (2D
+// scalar laws and limited Euler stages; the others are fused).
+static bool needs_lx(const za_problem& p) { return p.dim == 2 && (p.system != ZA_EULER || p.pp_limiter); }
 
 za_status za_ctx_create(const za_problem* p, void* stream, za_ctx** out) {
   if (!out) return ZA_ERR_ARG;
@@ -516,21 +576,21 @@ za_status za_ctx_create(const za_problem* p, void* stream, za_ctx** out) {
   c->q1 = (double*)ptr;
   if ((e = hipMalloc(&ptr, st_bytes)) != hipSuccess) { za_ctx_destroy(c); return ZA_ERR_NOMEM; }
   c->q2 = (double*)ptr;
-  if (p->dim == 2) {
+  if (needs_lx(*p)) {
     if ((e = hipMalloc(&ptr, st_bytes)) != hipSuccess) { za_ctx_destroy(c); return ZA_ERR_NOMEM; }
     c->lx = (double*)ptr;
   }
-  const size_t part_bytes = (size_t)c->part_blocks * NPART * sizeof(double) + 4096;   // a multiple of 16
-  if ((e = hipMalloc(&ptr, part_bytes + line_bytes(c->line_blocks))) != hipSuccess) {
+  // one allocation: partial sums, wave-speed rows, control blocks, exchange words
+  if ((e = hipMalloc(&ptr, kPartBytes + kRowsBytes + line_bytes(c->line_blocks))) != hipSuccess) {
     za_ctx_destroy(c);
     return ZA_ERR_NOMEM;
   }
   c->part = (double*)ptr;
-  c->line_xch = (unsigned long long*)((char*)ptr + part_bytes);
+  c->rows = (unsigned long long*)((char*)ptr + kPartBytes);
+  c->ctl = (DevCtl*)(c->rows + SP_SETS * SP_SET);
+  c->line_xch = (unsigned long long*)((char*)ptr + kPartBytes + kRowsBytes);
   line_init(c);
-  if ((e = hipMalloc(&ptr, sizeof(DevCtl))) != hipSuccess) { za_ctx_destroy(c); return ZA_ERR_NOMEM; }
-  c->ctl = (DevCtl*)ptr;
-  launch_ctl_reset(c);
+  launch_ctl(c, fresh_ctl());
   if ((e = hipGetLastError()) != hipSuccess) { za_ctx_destroy(c); return ZA_ERR_DEVICE; }
   *out = c;
   return ZA_OK;
@@ -548,7 +608,6 @@ za_status za_ctx_destroy(za_ctx* c) {
   if (c->q2) hipFree(c->q2);
   if (c->lx) hipFree(c->lx);
   if (c->part) hipFree(c->part);
-  if (c->ctl) hipFree(c->ctl);
   delete c;
   return ZA_OK;
 }
@@ -562,20 +621,7 @@ za_status za_ctx_set_stream(za_ctx* c, void* stream) {
 za_status za_rhs(za_ctx* c, const double* q, double* rhs) {
   if (!c || !q || !rhs || q == rhs) return ZA_ERR_ARG;
   c->speeds_valid = false;
-  if (line_ready(c) && c->line_blocks == 1) {
-    launch_line_rhs(c, q, rhs);
-    ZA_CHECK_LAUNCH(c, "rhs launch");
-    return ZA_OK;
-  }
-  launch_wave(c, q, FIN_RHS, 0);
-  SweepArgs a = base_args(c);
-  a.q = q;
-  a.out = rhs;
-  launch_x(c, MODE_RHS, a);
-  if (c->prob.dim == 2) {
-    a.lx = rhs;
-    launch_y(c, MODE_RHS, a);
-  }
+  launch_rhs(c, q, rhs);
   ZA_CHECK_LAUNCH(c, "rhs launch");
   return ZA_OK;
 }
@@ -583,10 +629,9 @@ za_status za_rhs(za_ctx* c, const double* q, double* rhs) {
 za_status za_rhs_fluxes(za_ctx* c, const double* q, double* fx, double* fy) {
   if (!c || !q || !fx) return ZA_ERR_ARG;
   c->speeds_valid = false;
-  launch_wave(c, q, FIN_RHS, 0);
-  SweepArgs a = base_args(c);
-  a.q = q;
-  a.out = fx;
+  launch_speeds(c, q, 0, nullptr);
+  SweepArgs a = rhs_args(c, q, fx);
+  begin_apart(c, MODE_FLUX, a);
   launch_x(c, MODE_FLUX, a);
   if (c->prob.dim == 2 && fy) {
     a.out = fy;
@@ -606,8 +651,7 @@ za_status za_step(za_ctx* c, double* q, double dt, double* dt_used) {
     launch_line(c, q, 1, &v);
     ZA_CHECK_LAUNCH(c, "step launch");
   } else {
-    launch_ctl(c, v);
-    if ((st = enqueue_step(c, q)) != ZA_OK) return st;
+    if ((st = enqueue_step(c, q, &v)) != ZA_OK) return st;
   }
   if (dt_used) {
     DevCtl h;
@@ -639,11 +683,12 @@ za_status za_solve(za_ctx* c, double* q, double t_final, int64_t max_steps, za_s
     if (max_steps > 0 && max_steps < n) n_run = max_steps;
     const int64_t n_equal = std::min<int64_t>(n_run, n - 1);
     h = start_ctl(dt, inf, n_equal);
-    launch_ctl(c, h);
+    const DevCtl v = h;
+    if (n_equal < 1) launch_ctl(c, v);
     for (int64_t s = 0; s < n_equal;) {
       const int64_t k = std::min<int64_t>(n_equal - s, line_ready(c) ? chunk : 64 * chunk);
       const bool more = s + k < n_equal;
-      if ((st = advance(c, q, k, nullptr, more, &h)) != ZA_OK) return st;
+      if ((st = advance(c, q, k, s == 0 ? &v : nullptr, more, &h)) != ZA_OK) return st;
       s += k;
       if (more && h.bad) break;
     }
@@ -684,7 +729,7 @@ za_status za_conserved_sums(za_ctx* c, const double* q, double* sums) {
   if (!c || !q || !sums) return ZA_ERR_ARG;
   c->speeds_valid = false;
   const size_t ncell = (size_t)c->prob.nx * c->prob.ny;
-  const int nblk = (int)std::min<size_t>((size_t)c->part_blocks * NPART, std::max<size_t>(1, (ncell + 4095) / 4096));
+  const int nblk = (int)std::min<size_t>((size_t)SUM_BLOCKS, std::max<size_t>(1, (ncell + 4095) / 4096));
   const size_t chunk = (ncell + nblk - 1) / nblk;
   std::vector<double> part(nblk);
   for (int comp = 0; comp < c->m; ++comp) {

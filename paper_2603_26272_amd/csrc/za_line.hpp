@@ -60,35 +60,8 @@ constexpr int LINE_SPEED_WORDS = LINE_MAX_BLOCKS * LINE_MAX_WAVES * 3 * 2;
 constexpr int LINE_HALO_WORDS = LINE_MAX_BLOCKS * 2 * LINE_HALO * 3 * 2;
 constexpr int LINE_WORDS = LINE_SPEED_WORDS + LINE_HALO_WORDS;
 
-__device__ __forceinline__ unsigned hi_word(double x) { return (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32); }
-__device__ __forceinline__ unsigned lo_word(double x) { return (unsigned)__builtin_bit_cast(unsigned long long, x); }
-__device__ __forceinline__ double from_words(unsigned lo, unsigned hi) {
-  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-
 // Maxima of NV values over lanes 0 .. LANES - 1 (4, 16 or 64), wave-uniform.
-// SIGNED = false: numbers >= 0 (or +inf), which order like their bit
-// patterns: the largest high word, then the largest low word beside it, one
-// DPP instruction per step where a 64-bit maximum needs three.  Speeds are of
-// that kind; the Buckley-Leverett range is not and takes the second form.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ unsigned dpp_max_u32(unsigned x) {
-  const unsigned y = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
-  return x > y ? x : y;
-}
-template <int LANES, int NV>
-__device__ __forceinline__ void words_max(unsigned (&m)[NV]) {
-#define ZA_STEP(CTRL, ROWS)                                                  \
-  {                                                                          \
-    _Pragma("unroll") for (int i = 0; i < NV; ++i) m[i] = dpp_max_u32<CTRL, ROWS>(m[i]); \
-  }
-  ZA_STEP(0x111, 0xf) ZA_STEP(0x112, 0xf)                   // row_shr 1, 2
-  if (LANES > 4) { ZA_STEP(0x114, 0xf) ZA_STEP(0x118, 0xf) }   // row_shr 4, 8
-  if (LANES > 16) { ZA_STEP(0x142, 0xa) ZA_STEP(0x143, 0xc) }  // row_bcast 15, 31
-#undef ZA_STEP
-#pragma unroll
-  for (int i = 0; i < NV; ++i) m[i] = (unsigned)__builtin_amdgcn_readlane((int)m[i], LANES - 1);
-}
+// SIGNED = false: numbers >= 0 (or +inf), by words_max.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp_max_f64(double x) {
   const int lo = (int)lo_word(x), hi = (int)hi_word(x);

@@ -4,9 +4,8 @@
 //
 // The only device memory the right-hand side needs beyond its input and
 // output is the wave-speed reduction: the per-block maxima of the reduction
-// pass (at most RED_BLOCKS_MAX blocks, whatever the grid size, since that
-// pass strides over the cells) and the control block that carries the
-// Lax-Friedrichs speeds to the sweeps.  Both live in `scratch`, a fixed
+// pass (at most SP_ROWS blocks, whatever the grid size, since that pass
+// strides over the cells) and a control block.  Both live in `scratch`, a fixed
 // device array of this file; each GPU holds its own copy until the process
 // ends.  Host code never passes the array's name to a kernel (on the host it
 // is only a stand-in): the device address of each GPU's copy is fetched once
@@ -22,9 +21,9 @@ using namespace za;
 
 namespace {
 
-// reduction partials, then the control block at a 256-byte boundary
-constexpr size_t kPartDoubles = (size_t)RED_BLOCKS_MAX * NPART;
-constexpr size_t kCtlOffset = (kPartDoubles * sizeof(double) + 255) / 256 * 256;
+// wave-speed rows, then the control block (of which only the flag of an
+// inadmissible state is written)
+constexpr size_t kCtlOffset = (size_t)SP_ROWS * SP_STRIDE * sizeof(unsigned long long);
 constexpr size_t kScratchBytes = kCtlOffset + 256;
 static_assert(sizeof(DevCtl) <= 256, "control block larger than its scratch slot");
 
@@ -60,22 +59,9 @@ extern "C" za_status za_rhs_noalloc(const za_problem* p, const double* q, double
   if (!base) return ZA_ERR_DEVICE;
   za_ctx c;   // no workspace: the scratch array stands in for it
   init_shape(&c, p, (hipStream_t)hip_stream);
-  if (c.red_blocks > RED_BLOCKS_MAX) return ZA_ERR_ARG;   // the scratch holds RED_BLOCKS_MAX rows
-  c.part = reinterpret_cast<double*>(base);
+  if (c.red_blocks > SP_ROWS) return ZA_ERR_ARG;   // the scratch holds SP_ROWS rows
+  c.rows = reinterpret_cast<unsigned long long*>(base);
   c.ctl = reinterpret_cast<DevCtl*>(base + kCtlOffset);
-  if (c.line_blocks == 1) {
-    launch_line_rhs(&c, q, rhs);
-    return hipGetLastError() == hipSuccess ? ZA_OK : ZA_ERR_DEVICE;
-  }
-  launch_ctl_reset(&c);
-  launch_wave(&c, q, FIN_RHS, 0);
-  SweepArgs a = base_args(&c);
-  a.q = q;
-  a.out = rhs;
-  launch_x(&c, MODE_RHS, a);
-  if (p->dim == 2) {
-    a.lx = rhs;
-    launch_y(&c, MODE_RHS, a);
-  }
+  launch_rhs(&c, q, rhs);
   return hipGetLastError() == hipSuccess ? ZA_OK : ZA_ERR_DEVICE;
 }

@@ -1,4 +1,4 @@
-// Sweeps of the fourth-, eighth- and tenth-order central-upwind schemes
+// Separate sweeps of the fourth-, eighth- and tenth-order central-upwind schemes
 // (r = 2, 4, 5; Appendix A) in FP64: the WENO-ZA6 kernels and launch shapes
 // with the stencil half-width as a template parameter; Z weights with an
 // occupancy target, the other weight variants (and flux output) through the
@@ -21,8 +21,11 @@ template <> struct OrderWaves<5> { enum { x = 2, y = 2 }; };
 
 template <int SYS, int M, int R, int WV>
 void x_any(za_ctx* c, int mode, const SweepArgs& a, const CfgArg<double>& cfg, dim3 grid) {
-  switch (mode) {
-    case MODE_FLUX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_FLUX, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
+  if (mode == MODE_FLUX) {
+    hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_FLUX, WV, R>), grid, dim3(256), 0, c->stream, a, cfg);
+    return;
+  }
+  if constexpr (M != 4) switch (mode) {
     case MODE_RHS: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_RHS, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
     case MODE_LX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_LX, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
     default: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_STAGE, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
@@ -30,13 +33,14 @@ void x_any(za_ctx* c, int mode, const SweepArgs& a, const CfgArg<double>& cfg, d
 }
 
 template <int SYS, int M, int R>
-void x_sys(za_ctx* c, int mode, const SweepArgs& a) {
+void x_sys(za_ctx* c, int mode, SweepArgs a) {
   const CfgArg<double> cfg = make_cfg<double>(c->prob);
   const int nseg = (a.g.nx + XS_CELLS - 1) / XS_CELLS;
   const long long waves = (long long)a.g.ny * nseg;
   const dim3 grid((unsigned)((waves + 3) / 4)), blk(256);
+  a.nblk = (int)grid.x;
   constexpr int XW = OrderWaves<R>::x;
-  if (!general_weights(c->prob) && mode != MODE_FLUX) {
+  if constexpr (M != 4) if (!general_weights(c->prob) && mode != MODE_FLUX) {
     switch (mode) {
       case MODE_RHS: hipLaunchKernelGGL((k_sweep_x_r<SYS, M, double, MODE_RHS, WV_Z1, R, XW>), grid, blk, 0, c->stream, a, cfg); break;
       case MODE_LX: hipLaunchKernelGGL((k_sweep_x_r<SYS, M, double, MODE_LX, WV_Z1, R, XW>), grid, blk, 0, c->stream, a, cfg); break;
@@ -50,8 +54,11 @@ void x_sys(za_ctx* c, int mode, const SweepArgs& a) {
 
 template <int SYS, int M, int R, int WV>
 void y_any(za_ctx* c, int mode, const SweepArgs& a, const CfgArg<double>& cfg, dim3 grid) {
-  switch (mode) {
-    case MODE_FLUX: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, double, MODE_FLUX, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
+  if (mode == MODE_FLUX) {
+    hipLaunchKernelGGL((k_sweep_y_any<SYS, M, double, MODE_FLUX, WV, R>), grid, dim3(256), 0, c->stream, a, cfg);
+    return;
+  }
+  if constexpr (M != 4) switch (mode) {
     case MODE_RHS: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, double, MODE_RHS, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
     default: hipLaunchKernelGGL((k_sweep_y_any<SYS, M, double, MODE_STAGE, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
   }
@@ -62,7 +69,7 @@ void y_sys(za_ctx* c, int mode, const SweepArgs& a) {
   const CfgArg<double> cfg = make_cfg<double>(c->prob);
   const dim3 grid((unsigned)((a.g.nx + 63) / 64), (unsigned)((a.g.ny + a.ytile - 1) / a.ytile)), blk(256);
   constexpr int YW = OrderWaves<R>::y;
-  if (!general_weights(c->prob) && mode != MODE_FLUX) {
+  if constexpr (M != 4) if (!general_weights(c->prob) && mode != MODE_FLUX) {
     if (mode == MODE_RHS)
       hipLaunchKernelGGL((k_sweep_y_r<SYS, M, double, MODE_RHS, WV_Z1, R, YW>), grid, blk, 0, c->stream, a, cfg);
     else
@@ -113,19 +120,15 @@ void launch_y_order(za_ctx* c, int mode, const SweepArgs& a) {
   }
 }
 
-// Resident blocks per CU of the stage y-sweep of this order (for the band
-// height); 0 if unknown.
+// Resident blocks per CU of the stage y-sweep of this order (scalar laws;
+// for the band height); 0 if unknown.
 int order_y_blocks_per_cu(const za_problem& p) {
   const void* fn = nullptr;
   const bool gp = general_weights(p), sq = gp && square_powers(p);
-#define ZA_YFN(R)                                                                                      \
-  (p.system == ZA_EULER                                                                                \
-       ? (sq   ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_EULER, 4, double, MODE_STAGE, WV_SQUARE, R>) \
-          : gp ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_EULER, 4, double, MODE_STAGE, WV_GENERAL, R>) \
-               : reinterpret_cast<const void*>(&k_sweep_y_r<SYS_EULER, 4, double, MODE_STAGE, WV_Z1, R, OrderWaves<R>::y>)) \
-       : (sq   ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_ADV, 1, double, MODE_STAGE, WV_SQUARE, R>)   \
-          : gp ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_ADV, 1, double, MODE_STAGE, WV_GENERAL, R>)   \
-               : reinterpret_cast<const void*>(&k_sweep_y_r<SYS_ADV, 1, double, MODE_STAGE, WV_Z1, R, OrderWaves<R>::y>)))
+#define ZA_YFN(R)                                                                                          \
+  (sq   ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_ADV, 1, double, MODE_STAGE, WV_SQUARE, R>)  \
+   : gp ? reinterpret_cast<const void*>(&k_sweep_y_any<SYS_ADV, 1, double, MODE_STAGE, WV_GENERAL, R>) \
+        : reinterpret_cast<const void*>(&k_sweep_y_r<SYS_ADV, 1, double, MODE_STAGE, WV_Z1, R, OrderWaves<R>::y>))
   switch (order_of(p)) {
     case 2: fn = ZA_YFN(2); break;
     case 4: fn = ZA_YFN(4); break;

@@ -30,38 +30,33 @@
 #include <vector>
 
 #include "za.h"
+#include "za_fused.hpp"
 #include "za_internal.hpp"
-#include "za_kernels.hpp"
 
 namespace zs {
 using namespace za;
 
 constexpr int MAX_SLOTS = 256;  // per class
 constexpr int NCLASS = 4;       // (1D, 2D) x (FP64, FP32 reconstruction)
-constexpr int SERVE_YTILE = 8 * YS_ROWS - 1; // default y-sweep rows per block in batches (a whole number of steps)
+constexpr int SERVE_STEPS = 8;   // most steps of a fused 2D block (bands of 4 s - 1 rows)
 
 struct SlotDesc {
   double* st;        // the request's state (Q^n, then the result)
   double* q1;        // RK3 stage states
   double* q2;
-  double* lx;        // 2D: x-sweep partial RHS
-  double* part;      // wave-speed maxima per stage-kernel block
-  DevCtl* ctl;       // the request's control block
+  unsigned long long* rows;   // wave-speed rows, a set per stage
+  DevCtl* ctl;       // the request's control block (copies MAX_SLOTS apart, one per stage)
   Geom g;
   Phys ph;
   double eps16, eps4, mu0x2;
-  int xblocks;       // x-sweep blocks
-  int ystrips;       // y-sweep: 64-column strips
-  int yblocks;       // y-sweep blocks (strips x tiles)
-  int stage_blocks;  // rows of wave-speed maxima the kernel that writes a stage state leaves
-  int xl_chunks;     // FP64: chunks per segment of the looped x-sweep
-  int ytile;         // 2D: y-sweep rows per block (band height)
+  int blocks;        // blocks of a stage
+  int strips, bands; // 2D: of the fused stage
+  int xl_chunks;     // 1D FP64: chunks per segment of the looped sweep
 };
 
 struct BatchTable {
-  int n, xtot, ytot, pad;
-  int xoff[MAX_SLOTS + 1];
-  int yoff[MAX_SLOTS + 1];
+  int n, tot;
+  int off[MAX_SLOTS + 1];
   SlotDesc s[MAX_SLOTS];
 };
 
@@ -74,20 +69,27 @@ __device__ __forceinline__ int find_slot(const int* __restrict__ off, int n, int
   return lo;
 }
 
-__device__ __forceinline__ SweepArgs slot_args(const SlotDesc& d, int stage, bool lx_out) {
+__device__ __forceinline__ SweepArgs slot_args(const SlotDesc& d, int stage) {
+  const int nxt = stage == 2 ? 0 : stage + 1, zero = stage == 0 ? 2 : stage - 1;
   SweepArgs a;
   a.q = stage == 0 ? d.st : (stage == 1 ? d.q1 : d.q2);
   a.qn = d.st;
-  a.lx = d.lx;
-  a.out = lx_out ? d.lx : (stage == 0 ? d.q1 : (stage == 1 ? d.q2 : d.st));
-  a.ctl = d.ctl;
+  a.lx = nullptr;
+  a.out = stage == 0 ? d.q1 : (stage == 1 ? d.q2 : d.st);
+  a.cin = d.ctl + stage * MAX_SLOTS;
+  a.ctl = d.ctl + nxt * MAX_SLOTS;
+  a.sp_in = d.rows + stage * SP_SET;
+  a.sp_rows = SP_ROWS;
+  a.sp_out = d.rows + nxt * SP_SET;
+  a.sp_zero = d.rows + zero * SP_SET;
+  a.kind = stage == 0 ? FIN_STAGE0 : (stage == 1 ? FIN_STAGEK : FIN_STAGE2);
+  a.nblk = d.blocks;
   a.g = d.g;
   a.ph = d.ph;
   a.ca = stage == 0 ? 0.0 : (stage == 1 ? 0.75 : 1.0 / 3.0);
   a.cb = stage == 0 ? 1.0 : (stage == 1 ? 0.25 : 2.0 / 3.0);
-  a.check_active = 1;
-  a.ytile = d.ytile;
-  a.part = d.part;
+  a.check_run = 0;
+  a.ytile = d.bands;
   a.xl_chunks = d.xl_chunks;
   return a;
 }
@@ -110,64 +112,32 @@ __device__ __forceinline__ CfgArg<T> slot_cfg(const SlotDesc& d) {
   return c;
 }
 
-#ifndef ZA_SRV_XS_WAVES
-#define ZA_SRV_XS_WAVES 3   // the slot lookup costs registers: four waves per SIMD would spill
-#endif
-template <int M, class T>
-__global__ __launch_bounds__(256, ZA_SRV_XS_WAVES) void kb_sweep_x(const BatchTable* __restrict__ tab, int stage) {
+// 1D stages: the one-shot sweep (FP32 reconstruction) or the looped one (FP64).
+__global__ __launch_bounds__(256, 3) void kb_line32(const BatchTable* __restrict__ tab, int stage) {
   const int b = blockIdx.x;
-  if (b >= tab->xtot) return;
-  const int s = find_slot(tab->xoff, tab->n, b);
+  if (b >= tab->tot) return;
+  const int s = find_slot(tab->off, tab->n, b);
   const SlotDesc& d = tab->s[s];
-  const SweepArgs a = slot_args(d, stage, M == 4);
-  const CfgArg<T> cfg = slot_cfg<T>(d);
-  if (M == 4)
-    sweep_x_body<SYS_EULER, M, T, MODE_LX, WV_Z1>(a, cfg, b - tab->xoff[s]);
-  else
-    sweep_x_body<SYS_EULER, M, T, MODE_STAGE, WV_Z1>(a, cfg, b - tab->xoff[s]);
+  sweep_x_body<SYS_EULER, 3, float, MODE_STAGE, WV_Z1>(slot_args(d, stage), slot_cfg<float>(d), b - tab->off[s]);
 }
-
-// FP64 classes: the looped x-sweep (2D: partial stage; 1D: the whole stage
-// and one row of wave-speed maxima per wavefront).
-template <int M>
-__global__ __launch_bounds__(256, 3) void kb_sweep_xl(const BatchTable* __restrict__ tab, int stage) {
+__global__ __launch_bounds__(256, 3) void kb_line64(const BatchTable* __restrict__ tab, int stage) {
   const int b = blockIdx.x;
-  if (b >= tab->xtot) return;
-  const int s = find_slot(tab->xoff, tab->n, b);
+  if (b >= tab->tot) return;
+  const int s = find_slot(tab->off, tab->n, b);
   const SlotDesc& d = tab->s[s];
-  const SweepArgs a = slot_args(d, stage, M == 4);
-  const CfgArg<double> cfg = slot_cfg<double>(d);
-  sweep_xl_body<SYS_EULER, M, WV_Z1, M == 4 ? MODE_LX : MODE_STAGE>(a, cfg, b - tab->xoff[s]);
+  sweep_xl_body<SYS_EULER, 3, WV_Z1, MODE_STAGE>(slot_args(d, stage), slot_cfg<double>(d), b - tab->off[s]);
 }
 
-template <class T>
-__global__ __launch_bounds__(256, ZA_YS_WAVES) void kb_sweep_y(const BatchTable* __restrict__ tab, int stage) {
+// 2D stages.
+template <class T, int WAVES>
+__global__ __launch_bounds__(64 * FU_NW, WAVES) void kb_fused(const BatchTable* __restrict__ tab, int stage) {
   const int b = blockIdx.x;
-  if (b >= tab->ytot) return;
-  const int s = find_slot(tab->yoff, tab->n, b);
+  if (b >= tab->tot) return;
+  const int s = find_slot(tab->off, tab->n, b);
   const SlotDesc& d = tab->s[s];
-  const SweepArgs a = slot_args(d, stage, false);
-  const CfgArg<T> cfg = slot_cfg<T>(d);
-  const int local = b - tab->yoff[s];
-  sweep_y_body<SYS_EULER, 4, T, MODE_STAGE, WV_Z1>(a, cfg, local % d.ystrips,
-                                                   local / d.ystrips, d.ystrips);
-}
-
-__global__ __launch_bounds__(64) void kb_final(const BatchTable* __restrict__ tab, int kind, int dim) {
-  const int s = blockIdx.x;
-  if (s >= tab->n) return;
-  const SlotDesc& d = tab->s[s];
-  wave_final_body(d.part, d.stage_blocks, d.ctl, d.g, d.ph, dim, kind, SYS_EULER);
-}
-
-__global__ __launch_bounds__(64) void kb_step_end(const BatchTable* __restrict__ tab) {
-  const int s = blockIdx.x;
-  if (s >= tab->n) return;
-  step_end_body(tab->s[s].ctl);
-}
-
-__global__ void k_ctl_set(DevCtl* ctl, DevCtl v) {
-  if (threadIdx.x == 0) *ctl = v;
+  const int local = b - tab->off[s];
+  fused_body<T, WV_Z1, 3, MODE_STAGE>(slot_args(d, stage), slot_cfg<T>(d), local % d.strips, local / d.strips,
+                                      d.strips);
 }
 
 // ---------------------------------------------------------------------------
@@ -264,17 +234,16 @@ static int class_of(const za_problem& p) { return (p.dim == 2 ? 2 : 0) + (p.prec
 static int ncomp(const za_problem& p) { return p.dim == 1 ? 3 : 4; }
 
 struct GraphKey {
-  int xcap, ycap, ncap;
-  bool operator<(const GraphKey& o) const {
-    return xcap != o.xcap ? xcap < o.xcap : (ycap != o.ycap ? ycap < o.ycap : ncap < o.ncap);
-  }
+  int cap;
+  bool operator<(const GraphKey& o) const { return cap < o.cap; }
 };
 
 struct Class {
   hipStream_t stream = nullptr;
   BatchTable* dtab = nullptr;
   BatchTable* htab[SERVE_DEPTH_MAX] = {};   // pinned: the table each queued burst uploaded
-  DevCtl* dctl = nullptr;               // MAX_SLOTS control blocks
+  DevCtl* dctl = nullptr;               // CTL_COPIES x MAX_SLOTS control blocks
+  unsigned long long* rows = nullptr;   // wave-speed rows, SP_SETS sets per slot
   DevCtl* hctl[SERVE_DEPTH_MAX] = {};       // pinned: control blocks after each queued burst
   hipEvent_t ev[SERVE_DEPTH_MAX] = {};
   std::deque<Burst> inflight;           // oldest first
@@ -322,69 +291,45 @@ struct za_server {
   int depth = SERVE_DEPTH;               // bursts queued per class
 };
 
-constexpr long long kServeMinWaves = 3072;   // 3 per SIMD of a 256-CU device
-
-// Chunks per segment of the looped x-sweep, which FP64 requests always use
-// (0 for FP32 reconstruction: the one-shot sweep), fixed at admission (its
-// wave-speed rows depend on it in 1D).  2D: the count that minimises the
-// work of a row, segments x (chunks + 0.15 for a segment's start), since a
-// row of n cells takes ceil(n / (64 nc - 1)) segments and a last segment of a
-// few cells costs as much as a full one (n = 1024: 3 chunks, 6 segments,
-// instead of 4 chunks, 5 segments), among the counts that leave a request
-// at least kServeMinWaves wavefronts (its latency when alone).  1D: up to
-// 4 chunks, which keeps many
-// wavefronts per request.  ZA_SRV_XL_CHUNKS in the environment forces a
-// value, clamped to 1 .. 64.
+// Chunks per segment of the looped 1D sweep of FP64 requests (0 for FP32
+// reconstruction: the one-shot sweep): up to 4, which keeps many wavefronts
+// per request.  ZA_SRV_XL_CHUNKS in the environment forces a value, clamped
+// to 1 .. 64.
 static int serve_xl_chunks(const za_problem& p) {
-  if (p.precision != ZA_FP64) return 0;
+  if (p.precision != ZA_FP64 || p.dim != 1) return 0;
   if (const char* e = std::getenv("ZA_SRV_XL_CHUNKS")) return std::max(1, std::min(std::atoi(e), 64));
-  if (p.dim == 1) return std::max(1, std::min(4, p.nx / 2048));
-  int best = 1;
-  double best_cost = -1.0;
-  for (int nc = 1; nc <= 16; ++nc) {
-    const long long seg = 64LL * nc - 1;
-    const long long segs = (p.nx + seg - 1) / seg;
-    // a request alone still fills three wavefronts per SIMD where it can
-    if (nc > 1 && (long long)p.ny * segs < kServeMinWaves) break;
-    const double cost = (double)segs * (nc + 0.15);
-    if (best_cost < 0.0 || cost < best_cost) { best_cost = cost; best = nc; }
-    if (seg >= p.nx) break;   // one segment per row from here on
-  }
-  return best;
+  return std::max(1, std::min(4, p.nx / 2048));
 }
 
-// Rows per y-sweep block of a 2D request, fixed at admission:
-// SERVE_YTILE, or ZA_SRV_YTILE from the environment (rounded to a whole
-// number of YS_ROWS-row steps, at least one).
-static int serve_ytile(const za_problem& p) {
-  (void)p;
+// Bands of a 2D request, fixed at admission: of up to SERVE_STEPS steps, as
+// tall as leave the request a block per CU (its latency when alone).
+// ZA_SRV_YTILE in the environment forces the rows of a band (rounded to a
+// whole number of steps, at least one).
+static int serve_bands(const za_problem& p, int strips) {
+  int s = SERVE_STEPS;
   if (const char* e = std::getenv("ZA_SRV_YTILE")) {
-    const int v = std::max(1, std::atoi(e) / YS_ROWS);
-    return YS_ROWS * std::min(v, 256) - 1;
+    s = std::min(std::max(1, std::atoi(e) / FU_NW), 256);
+  } else {
+    while (s > 1 && (long long)strips * ((p.ny + FU_NW * s - 2) / (FU_NW * s - 1)) < 256) --s;
   }
-  return SERVE_YTILE;
+  return (p.ny + FU_NW * s - 2) / (FU_NW * s - 1);
 }
 
-static size_t footprint(const za_problem& p, int* stage_blocks, int* xblocks, int* ystrips, int* yblocks,
-                        int* xl_chunks, int* ytile) {
-  const int m = ncomp(p);
-  const size_t S = (size_t)m * p.nx * p.ny * sizeof(double);
-  *xl_chunks = serve_xl_chunks(p);
-  *ytile = serve_ytile(p);
-  const long long xw = *xl_chunks > 0 ? xl_waves(p.nx, p.ny, *xl_chunks)
-                                      : (long long)p.ny * ((p.nx + XS_CELLS - 1) / XS_CELLS);
-  *xblocks = (int)((xw + 3) / 4);
+// The launch shape of a request, and its device bytes in the pool.
+static size_t footprint(const za_problem& p, SlotDesc* d) {
+  const size_t S = (size_t)ncomp(p) * p.nx * p.ny * sizeof(double);
+  d->xl_chunks = serve_xl_chunks(p);
+  d->strips = d->bands = 0;
   if (p.dim == 2) {
-    *ystrips = (p.nx + 63) / 64;
-    *yblocks = *ystrips * ((p.ny + *ytile - 1) / *ytile);
-    *stage_blocks = *yblocks;
+    d->strips = (p.nx + FU_COLS - 1) / FU_COLS;
+    d->bands = serve_bands(p, d->strips);
+    d->blocks = d->strips * d->bands;
   } else {
-    *ystrips = 0;
-    *yblocks = 0;
-    *stage_blocks = *xl_chunks > 0 ? (int)xw : *xblocks;
+    const long long w = d->xl_chunks > 0 ? xl_waves(p.nx, p.ny, d->xl_chunks)
+                                         : (long long)p.ny * ((p.nx + XS_CELLS - 1) / XS_CELLS);
+    d->blocks = (int)((w + 3) / 4);
   }
-  const size_t part = ((size_t)*stage_blocks * NPART * sizeof(double) + 255) & ~size_t(255);
-  return (p.dim == 2 ? 4 : 3) * ((S + 255) & ~size_t(255)) + part;
+  return 3 * ((S + 255) & ~size_t(255));
 }
 
 static int pow2_cap(int n, int lo) {
@@ -397,33 +342,20 @@ static int pow2_cap(int n, int lo) {
 // the table h, which the device table holds by the time the step runs.
 static void enqueue_class_step(Class& C, int c, const GraphKey& key) {
   const bool two_d = c >= 2, fp32 = (c & 1) != 0;
+  const dim3 grid(key.cap), blk(256);
   for (int s = 0; s < 3; ++s) {
-    hipLaunchKernelGGL(kb_final, dim3(key.ncap), dim3(64), 0, C.stream, C.dtab, s == 0 ? FIN_STAGE0 : FIN_STAGEK,
-                       two_d ? 2 : 1);
-    if (two_d) {
-      if (fp32) {
-        hipLaunchKernelGGL((kb_sweep_x<4, float>), dim3(key.xcap), dim3(256), 0, C.stream, C.dtab, s);
-        hipLaunchKernelGGL((kb_sweep_y<float>), dim3(key.ycap), dim3(256), 0, C.stream, C.dtab, s);
-      } else {
-        hipLaunchKernelGGL((kb_sweep_xl<4>), dim3(key.xcap), dim3(256), 0, C.stream, C.dtab, s);
-        hipLaunchKernelGGL((kb_sweep_y<double>), dim3(key.ycap), dim3(256), 0, C.stream, C.dtab, s);
-      }
-    } else {
-      if (fp32)
-        hipLaunchKernelGGL((kb_sweep_x<3, float>), dim3(key.xcap), dim3(256), 0, C.stream, C.dtab, s);
-      else
-        hipLaunchKernelGGL((kb_sweep_xl<3>), dim3(key.xcap), dim3(256), 0, C.stream, C.dtab, s);
-    }
+    if (two_d && fp32) hipLaunchKernelGGL((kb_fused<float, 4>), grid, blk, 0, C.stream, C.dtab, s);
+    else if (two_d) hipLaunchKernelGGL((kb_fused<double, 3>), grid, blk, 0, C.stream, C.dtab, s);
+    else if (fp32) hipLaunchKernelGGL(kb_line32, grid, blk, 0, C.stream, C.dtab, s);
+    else hipLaunchKernelGGL(kb_line64, grid, blk, 0, C.stream, C.dtab, s);
   }
-  hipLaunchKernelGGL(kb_step_end, dim3(key.ncap), dim3(64), 0, C.stream, C.dtab);
 }
 
 static hipError_t class_step(za_server* sv, int c, const BatchTable& h) {
   Class& C = sv->cls[c];
-  const bool two_d = c >= 2;
-  GraphKey key{pow2_cap(h.xtot, 64), two_d ? pow2_cap(h.ytot, 64) : 0, pow2_cap(h.n, 8)};
+  const GraphKey key{pow2_cap(h.tot, 64)};
   if (!sv->graphs) {   // direct launches: exact grids
-    enqueue_class_step(C, c, GraphKey{std::max(h.xtot, 1), two_d ? std::max(h.ytot, 1) : 0, std::max(h.n, 1)});
+    enqueue_class_step(C, c, GraphKey{std::max(h.tot, 1)});
     return hipGetLastError();
   }
   auto it = C.graphs.find(key);
@@ -445,18 +377,14 @@ static hipError_t class_step(za_server* sv, int c, const BatchTable& h) {
 
 static void rebuild_table(const Class& C, BatchTable& h) {
   h.n = (int)C.active.size();
-  int x = 0, y = 0;
+  int x = 0;
   for (int i = 0; i < h.n; ++i) {
     h.s[i] = C.active[i]->desc;
-    h.xoff[i] = x;
-    h.yoff[i] = y;
-    x += h.s[i].xblocks;
-    y += h.s[i].yblocks;
+    h.off[i] = x;
+    x += h.s[i].blocks;
   }
-  h.xoff[h.n] = x;
-  h.yoff[h.n] = y;
-  h.xtot = x;
-  h.ytot = y;
+  h.off[h.n] = x;
+  h.tot = x;
 }
 
 // Bytes of one state of r in the pinned staging pool.
@@ -518,8 +446,9 @@ static void admit(za_server* sv) {
     Class& C = sv->cls[r->cls];
     if (total >= sv->max_slots) break;
     if (C.free_slots.empty()) { ++it; continue; }
-    int sb, xb, ys, yb, xc, yt;
-    const size_t need = footprint(r->prob, &sb, &xb, &ys, &yb, &xc, &yt);
+    SlotDesc& d = r->desc;
+    std::memset(&d, 0, sizeof(d));
+    const size_t need = footprint(r->prob, &d);
     size_t off;
     if (!sv->pool.alloc(need, &off)) { ++it; continue; }
     r->off = off;
@@ -528,13 +457,10 @@ static void admit(za_server* sv) {
     C.free_slots.pop_back();
     const size_t S = ((r->m * r->ncell * sizeof(double)) + 255) & ~size_t(255);
     char* base = sv->pool_base + off;
-    SlotDesc& d = r->desc;
-    std::memset(&d, 0, sizeof(d));
     d.st = (double*)base;
     d.q1 = (double*)(base + S);
     d.q2 = (double*)(base + 2 * S);
-    d.lx = r->prob.dim == 2 ? (double*)(base + 3 * S) : nullptr;
-    d.part = (double*)(base + (r->prob.dim == 2 ? 4 : 3) * S);
+    d.rows = C.rows + (size_t)r->slot * SP_SETS * SP_SET;
     d.ctl = C.dctl + r->slot;
     const za_problem& p = r->prob;
     d.g.nx = p.nx; d.g.ny = p.ny; d.g.bc_x = p.bc_x; d.g.bc_y = p.bc_y;
@@ -547,7 +473,6 @@ static void admit(za_server* sv) {
     d.ph.cfl = p.cfl; d.ph.dt_rule = p.dt_rule; d.ph.lf_scalar = p.lf == ZA_LF_SCALAR ? 1 : 0;
     d.ph.pp = 0;   // requests with the limiter are not admitted
     d.eps16 = 16.0 * p.eps; d.eps4 = 4.0 * p.eps; d.mu0x2 = 2.0 * p.mu0;
-    d.xblocks = xb; d.ystrips = ys; d.yblocks = yb; d.stage_blocks = sb; d.xl_chunks = xc; d.ytile = yt;
     picked.push_back(r);
     ++total;
     it = sv->waiting.erase(it);
@@ -584,13 +509,13 @@ static void activate_uploaded(za_server* sv) {
     v.max_steps = r->n_steps;
     // stream order puts this after the queued bursts, which may still see
     // the slot's previous request (inactive) in their tables
-    hipLaunchKernelGGL(k_ctl_set, dim3(1), dim3(64), 0, C.stream, d.ctl, v);
+    const int nblk = (int)std::min<size_t>(SP_ROWS, (r->ncell + 255) / 256);
     if (r->prob.dim == 2)
-      hipLaunchKernelGGL((k_wave_partial<SYS_EULER, 4>), dim3(d.stage_blocks), dim3(256), 0, C.stream, d.st,
-                         r->ncell, d.ph, d.ctl, 0, d.part);
+      hipLaunchKernelGGL((k_speed_rows<SYS_EULER, 4>), dim3(nblk), dim3(256), 0, C.stream, d.st, r->ncell, d.ph,
+                         d.rows, 1, d.ctl, v);
     else
-      hipLaunchKernelGGL((k_wave_partial<SYS_EULER, 3>), dim3(d.stage_blocks), dim3(256), 0, C.stream, d.st,
-                         r->ncell, d.ph, d.ctl, 0, d.part);
+      hipLaunchKernelGGL((k_speed_rows<SYS_EULER, 3>), dim3(nblk), dim3(256), 0, C.stream, d.st, r->ncell, d.ph,
+                         d.rows, 1, d.ctl, v);
     if (hipGetLastError() != hipSuccess) {
       sv->err = "request start failed";
       finish_req(sv, r, ZA_ERR_DEVICE);
@@ -838,8 +763,12 @@ za_status za_server_create(size_t hbm_budget_bytes, int32_t max_slots, int32_t d
     if (hipStreamCreateWithFlags(&C.stream, hipStreamNonBlocking) != hipSuccess) return fail(ZA_ERR_DEVICE);
     if (hipMalloc(&p, sizeof(BatchTable)) != hipSuccess) return fail(ZA_ERR_NOMEM);
     C.dtab = (BatchTable*)p;
-    if (hipMalloc(&p, MAX_SLOTS * sizeof(DevCtl)) != hipSuccess) return fail(ZA_ERR_NOMEM);
+    if (hipMalloc(&p, CTL_COPIES * MAX_SLOTS * sizeof(DevCtl)) != hipSuccess) return fail(ZA_ERR_NOMEM);
     C.dctl = (DevCtl*)p;
+    // a class never holds more than max_slots requests, in its lowest slots
+    if (hipMalloc(&p, (size_t)max_slots * SP_SETS * SP_SET * sizeof(unsigned long long)) != hipSuccess)
+      return fail(ZA_ERR_NOMEM);
+    C.rows = (unsigned long long*)p;
     for (int b = 0; b < SERVE_DEPTH_MAX; ++b) {
       if (hipHostMalloc(&p, sizeof(BatchTable), hipHostMallocDefault) != hipSuccess) return fail(ZA_ERR_NOMEM);
       C.htab[b] = (BatchTable*)p;
@@ -869,8 +798,8 @@ za_status za_server_submit(za_server* sv, const za_problem* p, const double* q0,
   // batches run the paper's weights (Z type, p = 1, mu = 1) on the Euler equations
   if (p->system != ZA_EULER || general_weights(*p) || order_of(*p) != 3 || p->pp_limiter)
     return ZA_ERR_UNSUPPORTED;
-  int sb, xb, ys, yb, xc, yt;
-  if (footprint(*p, &sb, &xb, &ys, &yb, &xc, &yt) > sv->budget) return ZA_ERR_NOMEM;
+  SlotDesc shape;
+  if (footprint(*p, &shape) > sv->budget) return ZA_ERR_NOMEM;
   auto r = std::make_unique<Req>();
   r->prob = *p;
   r->cls = class_of(*p);
@@ -975,6 +904,7 @@ za_status za_server_destroy(za_server* sv) {
     for (auto& kv : C.graphs) (void)hipGraphExecDestroy(kv.second);
     if (C.dtab) (void)hipFree(C.dtab);
     if (C.dctl) (void)hipFree(C.dctl);
+    if (C.rows) (void)hipFree(C.rows);
     for (int b = 0; b < SERVE_DEPTH_MAX; ++b) {
       if (C.htab[b]) (void)hipHostFree(C.htab[b]);
       if (C.hctl[b]) (void)hipHostFree(C.hctl[b]);

@@ -1,0 +1,87 @@
+"""GPU: the fused 2D Euler stage (both sweeps of a stage in one kernel, strips
+of at most 63 columns, bands of rows, four interface rows per step) at the
+edges of its tiles: widths around one and two strips and around the halo
+columns that one wavefront loads in turn, heights around one step and one
+band, grids narrower than a stencil, both boundary conditions, every order
+and weight kind, and both precisions.  Right-hand sides against the oracle
+at the bar of the other right-hand-side tests (1e-11 of the component scale;
+FP32 reconstruction: 3e-5 of the flux scale over the cell size), three steps
+at the state bar (1e-10, FP64)."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from paper_2603_26272_amd import workloads as W
+from paper_2603_26272_amd.problem import PERIODIC, TRANSMISSIVE
+
+from tests.test_gpu_parity import assert_close
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SHAPES = [(1, 1), (2, 5), (5, 2), (7, 3), (57, 4), (58, 7), (59, 8), (62, 3), (63, 5), (64, 11), (65, 12), (125, 4),
+          (126, 6), (127, 33), (190, 9), (16, 130)]
+KINDS = [dict(), dict(order=2), dict(order=4), dict(order=5), dict(weight_L=0.0, p=2.0), dict(affine_invariant=1),
+         dict(p=1.5), dict(order=5, weight_L=0.0, p=2.0), dict(precision=1, eps=1e-20, mu0=1e-8),
+         dict(precision=1, eps=1e-20, mu0=1e-8, weight_L=0.0, p=2.0), dict(lf=1)]
+
+
+def _data(nx, ny):
+    P, q0 = W.quadrants_2d(nx + 5 * ny, max(nx, 2), max(ny, 2))
+    q0 = np.ascontiguousarray(q0[:, :ny, :nx])
+    # a ripple rules out exactly tied indicators on tiny and periodic grids
+    x = np.arange(nx)[None, :] + 0.37 * np.arange(ny)[:, None]
+    q0[0] *= 1 + 1e-2 * np.sin(1.3 * x + 0.2)
+    return P.with_(nx=nx, ny=ny, xhi=nx / 64.0, yhi=ny / 64.0), q0
+
+
+@pytest.mark.parametrize("kind", KINDS, ids=lambda k: "-".join(f"{a}{b}" for a, b in k.items()) or "z")
+@pytest.mark.parametrize("bc", [TRANSMISSIVE, PERIODIC])
+def test_rhs_and_steps_against_oracle(kind, bc):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_26272_amd.za import Context, rhs_noalloc
+    for nx, ny in SHAPES:
+        P, q0 = _data(nx, ny)
+        P = P.with_(bc_x=bc, bc_y=bc, **kind)
+        f32 = P.precision == 1
+        tag = f"{nx}x{ny} {kind}"
+        ref, st = orc.rhs(P, q0)
+        assert st == 0
+        q = torch.from_numpy(q0).cuda()
+        with Context(P) as ctx:
+            got = ctx.rhs(q).cpu().numpy()
+            info = ctx.solve(q, 0.0, 3)
+        alone = rhs_noalloc(P, torch.from_numpy(q0).cuda()).cpu().numpy()
+        assert np.array_equal(alone, got), tag
+        if f32:
+            fx, fy, _ = orc.fluxes(P, q0)
+            scale = np.abs(fx).max(axis=(1, 2), keepdims=True) + np.abs(fy).max(axis=(1, 2), keepdims=True)
+            assert (np.abs(got - ref) <= 3e-5 * 64.0 * 2.0 * scale).all(), tag
+        else:
+            assert_close(got, ref, 1e-11 if nx > 5 and ny > 5 else 1e-10, tag)
+        rq, steps, t, st = orc.solve(P, q0, 0.0, 3)
+        assert st == 0 and info["steps"] == 3 == steps
+        if not f32:   # (FP32 states: the FP32 tests of test_gpu_parity and test_gpu_large)
+            assert_close(q.cpu().numpy(), rq, 1e-10, tag)
+
+
+def test_bands_do_not_change_the_result():
+    """A tall grid (many bands and steps per band) equals its pieces: a
+    periodic tile repeated vertically gives the tile's right-hand side."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_26272_amd.za import Context
+    P, q0 = _data(130, 37)
+    P = P.with_(bc_x=PERIODIC, bc_y=PERIODIC)
+    with Context(P) as ctx:
+        one = ctx.rhs(torch.from_numpy(q0).cuda()).cpu().numpy()
+    for k in (7, 61):
+        Pk = P.with_(ny=37 * k, yhi=P.yhi * k)
+        with Context(Pk) as ctx:
+            got = ctx.rhs(torch.from_numpy(np.tile(q0, (1, k, 1))).cuda()).cpu().numpy()
+        if Pk.dy == P.dy:
+            assert np.array_equal(got, np.tile(one, (1, k, 1)))
+        else:
+            assert_close(got, np.tile(one, (1, k, 1)), 1e-12, f"{k} tiles")
