@@ -94,7 +94,7 @@ size_t za_state_count(const za_problem* p) {
 
 // device bytes of the partial sums, and of the rows and control blocks
 static constexpr int SUM_BLOCKS = 6144;
-static constexpr size_t kPartBytes = (size_t)SUM_BLOCKS * sizeof(double);
+static constexpr size_t kPartBytes = 4 * (size_t)SUM_BLOCKS * sizeof(double);   // per component
 static constexpr size_t kRowsBytes = SP_SETS * SP_SET * sizeof(unsigned long long) + 1024;
 static_assert(CTL_COPIES * sizeof(DevCtl) <= 1024, "the control blocks");
 
@@ -731,15 +731,15 @@ za_status za_conserved_sums(za_ctx* c, const double* q, double* sums) {
   const size_t ncell = (size_t)c->prob.nx * c->prob.ny;
   const int nblk = (int)std::min<size_t>((size_t)SUM_BLOCKS, std::max<size_t>(1, (ncell + 4095) / 4096));
   const size_t chunk = (ncell + nblk - 1) / nblk;
-  std::vector<double> part(nblk);
+  hipLaunchKernelGGL(k_sum_partial, dim3(nblk, c->m), dim3(256), 0, c->stream, q, ncell, chunk, c->part);
+  ZA_CHECK_LAUNCH(c, "sum launch");
+  std::vector<double> part((size_t)nblk * c->m);
+  const hipError_t e =
+      hipMemcpyWithStream(part.data(), c->part, part.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream);
+  if (e != hipSuccess) return hip_fail(c, e, "copy sums");
   for (int comp = 0; comp < c->m; ++comp) {
-    hipLaunchKernelGGL(k_sum_partial, dim3(nblk), dim3(256), 0, c->stream, q + comp * ncell, ncell, chunk, c->part);
-    ZA_CHECK_LAUNCH(c, "sum launch");
-    hipError_t e = hipMemcpyAsync(part.data(), c->part, nblk * sizeof(double), hipMemcpyDeviceToHost, c->stream);
-    if (e != hipSuccess) return hip_fail(c, e, "copy sums");
-    if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return hip_fail(c, e, "synchronise");
     double s = 0.0;
-    for (int b = 0; b < nblk; ++b) s += part[b];
+    for (int b = 0; b < nblk; ++b) s += part[(size_t)comp * nblk + b];
     sums[comp] = s;
   }
   return ZA_OK;
