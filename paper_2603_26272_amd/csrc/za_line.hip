@@ -115,7 +115,8 @@ void line_shape(const za_problem& p, int* blocks, int* waves) {
   for (int w = std::min(4, max_waves); w <= max_waves; w *= 2) {
     const int cells = 64 * w - 1;
     const long long n = ((long long)p.nx + cells - 1) / cells;
-    if (n <= LINE_MAX_BLOCKS) {
+    // a quarter of the wavefronts that 256 CUs hold at the kernel's registers
+    if (n <= LINE_MAX_BLOCKS && n * w <= 64 * max_waves) {
       *blocks = (int)n;
       *waves = w;
       return;

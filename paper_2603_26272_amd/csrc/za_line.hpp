@@ -8,7 +8,7 @@
 // block: 2,900 cycles of fluxes, which four wavefronts on one CU issue at
 // 4.9 cycles per instruction, and 1,800 of update, records and reduction),
 // 1D Euler 4096 cells 9.7 -> 4.2 us (17 blocks: 2 us of it the round trip of
-// the exchange through memory).  Thread t of a block owns cell c0 + t
+// the exchange through memory), 32000 cells 9.9 -> 4.9 us (126 blocks).  Thread t of a block owns cell c0 + t
 // (its Q and Q^n stay in registers) and computes interface c0 + t; the
 // records of the block's cells and of R halo cells per side sit in LDS.  Per
 // stage: fluxes, one barrier, the update and the new records, the exchange
@@ -42,7 +42,13 @@ struct LineArgs {
   long long spin;            // wait limit, ticks of wall_clock64()
 };
 
-constexpr int LINE_MAX_BLOCKS = 64;
+// Four such launches at once (one per hardware queue) still fit the chip: the
+// host takes at most a quarter of the wavefronts that 256 CUs hold at the
+// kernel's registers (512 of 8 per CU, or 1024 of 16).
+constexpr int LINE_MAX_BLOCKS = 128;
+// Up to this many blocks every wavefront publishes its own maxima (one thread
+// waits for each); beyond, the block's are reduced first, one barrier more.
+constexpr int LINE_WAVE_BLOCKS = 64;
 constexpr int LINE_MAX_WAVES = 16;
 constexpr int LINE_HALO = 5;   // widest stencil half-width
 // Wavefronts that one block takes before a second one joins: a second
@@ -56,7 +62,7 @@ constexpr int LINE_ONE_BLOCK_SCALAR = 16;
 
 // Exchange words of one parity: per wavefront its 3 wave-speed maxima, per
 // block and side the R edge cells; two words per double.
-constexpr int LINE_SPEED_WORDS = LINE_MAX_BLOCKS * LINE_MAX_WAVES * 3 * 2;
+constexpr int LINE_SPEED_WORDS = LINE_WAVE_BLOCKS * LINE_MAX_WAVES * 3 * 2;
 constexpr int LINE_HALO_WORDS = LINE_MAX_BLOCKS * 2 * LINE_HALO * 3 * 2;
 constexpr int LINE_WORDS = LINE_SPEED_WORDS + LINE_HALO_WORDS;
 
@@ -170,6 +176,7 @@ struct LineBlock {
     T rec[NF * RECN];
     double fw[M][LB / 64 + 1];   // flux of each wavefront's first interface
     double sm[NV][16];           // maxima per wavefront
+    double sb[NV][16];           // ... of the block's own cells
     int dead;
   };
   Lds& s;
@@ -191,11 +198,22 @@ struct LineBlock {
       unsigned long long* const base = a.xch + (size_t)(tag & 1) * LINE_WORDS;
       unsigned long long* const sp = base;
       unsigned long long* const hl = base + LINE_SPEED_WORDS;
-      if (lane < 2 * NV) {
+      const bool per_block = P > LINE_WAVE_BLOCKS;
+      if (per_block) {
+        if (lane == 0) {
+#pragma unroll
+          for (int i = 0; i < NV; ++i) s.sb[i][wv] = v[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NV; ++i) v[i] = s.sb[i][lane & 15];
+        lanes_max<16, NV, SIGNED>(v);
+      }
+      if (lane < 2 * NV && (!per_block || wv == 0)) {
         double x = v[0];
 #pragma unroll
         for (int i = 1; i < NV; ++i) x = (lane >> 1) == i ? v[i] : x;
-        line_put(sp + (b * nw + wv) * 6 + lane, line_word(x, lane & 1, tag));
+        line_put(sp + (per_block ? b : b * nw + wv) * 6 + lane, line_word(x, lane & 1, tag));
       }
       if (own && (tid < R || tid >= n - R)) {
         // side 0: the block's first R cells, side 1: its last R
@@ -213,9 +231,9 @@ struct LineBlock {
         }
       }
       if (own) cell_record<SYS, M, 0, T>(q, a.ph, s.rec + R + tid, RECN);
-      // thread i waits for wavefront i's maxima, threads 0 .. 2R - 1 also for
-      // the halo cells
-      const bool need = tid < P * nw;
+      // thread i waits for wavefront (block) i's maxima, threads 0 .. 2R - 1
+      // also for the halo cells
+      const bool need = tid < (per_block ? P : P * nw);
       const bool left = tid < R;
       const bool hneed = tid < 2 * R && (left ? has_l : has_r);
       const int hk = left ? tid : tid - R;
@@ -297,7 +315,7 @@ __global__ __launch_bounds__(LB) void k_line_solve(LineArgs a, CfgArg<T> cfg) {
   if (!st.active) return;
   if (tid < 16) {
 #pragma unroll
-    for (int i = 0; i < B::NV; ++i) lds.sm[i][tid] = B::NONE;
+    for (int i = 0; i < B::NV; ++i) lds.sm[i][tid] = lds.sb[i][tid] = B::NONE;
   }
   if (tid == 0) lds.dead = 0;
   // record slots of this thread's stencil (ghost cells by index)
@@ -412,7 +430,7 @@ __global__ __launch_bounds__(LB) void k_line_rhs(LineArgs a, CfgArg<T> cfg) {
   B blk{lds, tid, lane, wv, (int)(blockDim.x >> 6), 1, 0, N, tid < N, false, false};
   if (tid < 16) {
 #pragma unroll
-    for (int i = 0; i < B::NV; ++i) lds.sm[i][tid] = B::NONE;
+    for (int i = 0; i < B::NV; ++i) lds.sm[i][tid] = lds.sb[i][tid] = B::NONE;
   }
   int off[2 * R];
 #pragma unroll

@@ -56,7 +56,7 @@ def _same(monkeypatch, P, q0, **kw):
 
 @pytest.mark.parametrize("bc", [PERIODIC, TRANSMISSIVE])
 @pytest.mark.parametrize("N", [1, 2, 3, 5, 7, 63, 64, 65, 200, 255, 256, 511, 512, 513, 765, 1021, 4096, 16320,
-                               16321, 32704, 32705])
+                               16321, 32640, 32641, 32704, 32705])
 def test_euler_sizes(monkeypatch, N, bc):
     P, q0 = _data(EULER, N)
     _same(monkeypatch, P.with_(bc_x=bc), q0)
@@ -64,7 +64,7 @@ def test_euler_sizes(monkeypatch, N, bc):
 
 @pytest.mark.parametrize("bc", [PERIODIC, TRANSMISSIVE])
 @pytest.mark.parametrize("system", [ADVECTION, BURGERS, BUCKLEY])
-@pytest.mark.parametrize("N", [2, 64, 400, 1023, 1024, 5000, 65473])
+@pytest.mark.parametrize("N", [2, 64, 400, 1023, 1024, 5000, 16321, 32641, 65408, 65472, 65473])
 def test_scalar_sizes(monkeypatch, system, N, bc):
     P, q0 = _data(system, N)
     _same(monkeypatch, P.with_(bc_x=bc), q0, steps=5)
