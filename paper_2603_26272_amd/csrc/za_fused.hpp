@@ -51,8 +51,7 @@ __device__ __forceinline__ void fused_body(const SweepArgs& a, const CfgArg<T>& 
   static_assert(NW * 16 == 64 && 2 * R - 1 <= 16, "one wavefront loads a step's last halo columns");
   __shared__ T ring[ROWS * RS];
   __shared__ double fb[NW + 1][4][FU_COLS];
-  StageLoads<SYS_EULER, 2> sl;
-  stage_load(a, sl);
+  __shared__ double sc[10];   // the stage's constants: speeds, dt, whether it runs
   const int lane = threadIdx.x & 63, w = wave_id();
   const int nx = a.g.nx, ny = a.g.ny;
   const size_t cs = (size_t)nx * ny;
@@ -67,13 +66,26 @@ __device__ __forceinline__ void fused_body(const SweepArgs& a, const CfgArg<T>& 
   const unsigned xa = bc_map_span(x0 - R + lane, x0 - R, 64, nx, a.g.bc_x);
   const unsigned xb = in1 ? bc_map(x0 - R + 64 + lane, nx, a.g.bc_x) : 0;
   const int xh = bc_map(x0 - R + 64 + (lane & 15), nx, a.g.bc_x);
-  SweepConst kx_, ky_;
-  {
-    constexpr int NPRO = (ROWS + NW - 1) / NW;
+  // The last wavefront prepares the stage's constants while the others build
+  // the records of the first rows (all of them doing both: 128^2 12.4 us a
+  // stage, now 11.7; 1024^2 FP32 54.6, 53.0).
+  if (w == NW - 1) {
+    StageLoads<SYS_EULER, 2> sl;
+    stage_load(a, sl);
+    SweepConst k0, k1;
+    const bool run = stage_begin(a, sl, by * gx + bx, 2, k0, k1, lane, 64);
+    if (lane == 0) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) { sc[s] = k0.al[s]; sc[4 + s] = k1.al[s]; }
+      sc[8] = k0.dt;
+      sc[9] = run ? 1.0 : 0.0;
+    }
+  } else {
+    constexpr int NPRO = (ROWS + NW - 2) / (NW - 1);
     double qa[NPRO][4], qb[NPRO][4];
 #pragma unroll
     for (int t = 0; t < NPRO; ++t) {
-      const int i = w + NW * t;
+      const int i = w + (NW - 1) * t;
       if (i < ROWS) {
         const size_t row = (size_t)bc_map(y0 - R + i, ny, a.g.bc_y) * nx;
         if (in0) {
@@ -86,10 +98,9 @@ __device__ __forceinline__ void fused_body(const SweepArgs& a, const CfgArg<T>& 
         }
       }
     }
-    if (!stage_begin(a, sl, by * gx + bx, 2, kx_, ky_)) return;   // behind those loads
 #pragma unroll
     for (int t = 0; t < NPRO; ++t) {
-      const int i = w + NW * t;
+      const int i = w + (NW - 1) * t;
       if (i < ROWS) {
         if (in0) euler_record2<T>(qa[t], (T)a.ph.gm1, ring + i * RS + lane, FU_RECS);
         if (in1) euler_record2<T>(qb[t], (T)a.ph.gm1, ring + i * RS + 64 + lane, FU_RECS);
@@ -97,6 +108,11 @@ __device__ __forceinline__ void fused_body(const SweepArgs& a, const CfgArg<T>& 
     }
   }
   __syncthreads();
+  if (scalar_of(sc[9]) == 0.0) return;
+  SweepConst kx_, ky_;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) { kx_.al[s] = scalar_of(sc[s]); ky_.al[s] = scalar_of(sc[4 + s]); }
+  kx_.dt = ky_.dt = scalar_of(sc[8]);
   const double kx = scalar_of(-(a.cb * kx_.dt) * a.g.inv_dx), ky = scalar_of(-(a.cb * ky_.dt) * a.g.inv_dy);
   int sb = w;                        // ring slot of row k - R
   int fk = w;                        // flux slot of interface row k

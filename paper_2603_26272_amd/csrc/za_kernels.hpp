@@ -581,11 +581,13 @@ __device__ __forceinline__ void stage_load(const SweepArgs& a, StageLoads<SYS, N
 }
 
 // The stage's constants from the rows of its input; false if the stage does
-// not run.  Every thread of the grid calls (bid: the block's index); block 0
-// stores the control block, all blocks together clear sp_zero.
+// not run.  Every thread of the grid calls, or one wavefront of each block
+// (bid: the block's index, t0 the thread's among the block's nt callers);
+// block 0 stores the control block, all blocks together clear sp_zero.
 template <int SYS, int NX = 2>
 __device__ __forceinline__ bool stage_begin(const SweepArgs& a, const StageLoads<SYS, NX>& L, int bid, int dim,
-                                            SweepConst& kx, SweepConst& ky) {
+                                            SweepConst& kx, SweepConst& ky, int t0 = threadIdx.x,
+                                            int nt = blockDim.x) {
   constexpr int NV = SpeedCount<SYS, NX>::value;
   unsigned long long best[NV];
 #pragma unroll
@@ -624,7 +626,7 @@ __device__ __forceinline__ bool stage_begin(const SweepArgs& a, const StageLoads
   ky.smax = sy;
   kx.mu = ky.mu = 0.0;
   kx.dt = ky.dt = 0.0;
-  const bool leader = bid == 0 && threadIdx.x == 0;
+  const bool leader = bid == 0 && t0 == 0;
   if (a.kind == FIN_RHS) {
     if (leader) {
 #pragma unroll
@@ -695,7 +697,7 @@ __device__ __forceinline__ bool stage_begin(const SweepArgs& a, const StageLoads
     o->stuck = 0; o->line_tag = in.line_tag;
   }
   if (run) {
-    for (int i = bid * blockDim.x + threadIdx.x; i < SP_SET; i += a.nblk * blockDim.x) a.sp_zero[i] = 0;
+    for (int i = bid * nt + t0; i < SP_SET; i += a.nblk * nt) a.sp_zero[i] = 0;
   }
   // scalar registers, as if loaded from the control block
   kx.dt = ky.dt = scalar_of(dt);
