@@ -27,15 +27,17 @@ void fused_shape(const za_problem& p, int* gx, int* gy) {
                        : r == 2 ? (int)FuWaves<double, WV_Z1, 2>::value : (int)FuWaves<double, WV_Z1, 5>::value;
   const int strips = (p.nx + FU_COLS - 1) / FU_COLS, cus = 256;
   double best = -1;
-  for (int s = 1; s <= 4096; ++s) {
-    const int h = FU_NW * s - 1;   // rows of a band of s steps
-    const int nb = (p.ny + h - 1) / h;
-    const long long m = ((long long)strips * nb + cus - 1) / cus;
+  // (bands of more than 256 steps only where the grid would have too many)
+  for (long long s = 1;; s = s < 256 ? s + 1 : 2 * s) {
+    const long long h = FU_NW * s - 1;   // rows of a band of s steps
+    const long long nb = (p.ny + h - 1) / h;
+    if (nb > 65535) continue;
+    const long long m = (strips * nb + cus - 1) / cus;
     const long long full = m / res, rest = m % res;
     const double idle = rest == 1 ? 1.5 : (rest == 2 && res > 2 ? 1.15 : 1.0);
     const double cost = full * (res * s + 2.0) + (rest ? idle * rest * s + 2.0 : 0.0);
-    if (best < 0 || cost < best) { best = cost; *gx = strips; *gy = nb; }
-    if (nb == 1) break;
+    if (best < 0 || cost < best) { best = cost; *gx = strips; *gy = (int)nb; }
+    if (m <= 1 || s >= 256) break;   // from here on only slower
   }
 }
 
