@@ -16,7 +16,7 @@
 // 181 to 85 bytes, records are built once, and a stage is one launch.  Per
 // stage, before -> now (with the separate reduction launch before): 2048^2
 // FP64 277 -> 246 us, 512^2 39 -> 28 us, 128^2 24.7 -> 11.3 us; 2048^2 FP32
-// 208 -> 180 us; 512^2 JS weights (without pow()) 53 -> 42 us, tenth order 72
+// 208 -> 174 us; 512^2 JS weights (without pow()) 53 -> 42 us, tenth order 72
 // -> 65 us.
 //
 // Shape.  64 x-interfaces take 63 columns; the y-interfaces of the same
@@ -47,6 +47,10 @@ __device__ __forceinline__ void fused_body(const SweepArgs& a, const CfgArg<T>& 
   constexpr int NW = FU_NW, NF = Layout2<T>::NF;
   constexpr int FU_RECS = FU_COLS + 2 * R;                       // records per ring row
   constexpr int ROWS = NW + 2 * R - 1, RS = NF * FU_RECS;        // ring rows, row stride
+  // FP32 records leave the registers to issue a step's loads before its
+  // x-fluxes (1024^2 53.0 -> 51.1 us a stage, 2048^2 177 -> 174); FP64 just
+  // fits them too and gains nothing (2048^2 251.3, 250.6).
+  constexpr bool EARLY = sizeof(T) == sizeof(float) && WV == WV_Z1 && R == 3;
   constexpr bool REREAD = sizeof(T) == sizeof(double) && MODE == MODE_STAGE;
   static_assert(NW * 16 == 64 && 2 * R - 1 <= 16, "one wavefront loads a step's last halo columns");
   __shared__ T ring[ROWS * RS];
@@ -145,9 +149,33 @@ __device__ __forceinline__ void fused_body(const SweepArgs& a, const CfgArg<T>& 
     const bool upd = row_in && lane < wc;
     const size_t ro = (size_t)r * nx + x0;   // wave-uniform
     const unsigned ul = lane;
-    double part[4], qn[4];
+    // loads for the end of the step
+    const int hrow = lane >> 4, rh = k - w + hrow + NW + R - 1;
+    // the last halo columns of all the step's new rows: one wavefront in turn
+    const bool hal = w == (st & (NW - 1)) && (lane & 15) + 64 < wc + 2 * R && rh <= ylast + R - 1;
+    double qn[4], qa[4], qb[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) qn[c] = 0.0;
+    auto loads = [&]() {
+      if (MODE == MODE_STAGE && upd && a.ca != 0.0) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) qn[c] = gptr(a.qn + c * cs + ro)[ul];
+      }
+      if (need) {
+        const size_t row = (size_t)bc_map_span(rn, rn, 1, ny, a.g.bc_y) * nx;
+        if (in0) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) qa[c] = gptr(a.q + c * cs + row)[xa];
+        }
+      }
+      if (hal) {
+        const size_t o = (size_t)bc_map(rh, ny, a.g.bc_y) * nx + xh;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) qb[c] = gptr(a.q)[c * cs + o];
+      }
+    };
+    if (EARLY) loads();
+    double part[4];
     if (row_in) {
       double qc[4];
       if (MODE == MODE_STAGE && upd) {
@@ -178,29 +206,8 @@ __device__ __forceinline__ void fused_body(const SweepArgs& a, const CfgArg<T>& 
         }
       }
     }
-    // loads for the end of the step, behind the fluxes: other blocks' wavefronts
-    // cover them, and held across the fluxes their registers would spill
-    if (MODE == MODE_STAGE && upd && a.ca != 0.0) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) qn[c] = gptr(a.qn + c * cs + ro)[ul];
-    }
-    double qa[4];
-    if (need) {
-      const size_t row = (size_t)bc_map_span(rn, rn, 1, ny, a.g.bc_y) * nx;
-      if (in0) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) qa[c] = gptr(a.q + c * cs + row)[xa];
-      }
-    }
-    // the last halo columns of all the step's new rows: one wavefront in turn
-    const int hrow = lane >> 4, rh = k - w + hrow + NW + R - 1;
-    const bool hal = w == (st & (NW - 1)) && (lane & 15) + 64 < wc + 2 * R && rh <= ylast + R - 1;
-    double qb[4];
-    if (hal) {
-      const size_t o = (size_t)bc_map(rh, ny, a.g.bc_y) * nx + xh;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) qb[c] = gptr(a.q)[c * cs + o];
-    }
+    // behind the fluxes: other blocks' wavefronts cover the loads
+    if (!EARLY) loads();
     __syncthreads();   // the flux rows are in place, the ring has been read
     if (need) {
       // row rn takes the slot of row k - R
