@@ -12,7 +12,7 @@ using namespace za;
 // the launch 1 more.  (Fitted over grids from 400^2 to 2048^2: FP64 stages
 // take 9.5 us + 3.2 us per step; 1300 x 900: 76 us with the choice below, 98
 // with one block per CU.)
-void fused_shape(const za_problem& p, int* gx, int* gy) {
+void fused_shape(const za_problem& p, int cus, int* gx, int* gy) {
   *gx = *gy = 0;
   if (p.dim != 2 || p.system != ZA_EULER) return;
   const bool f32 = p.precision == ZA_FP32_RECON;
@@ -25,7 +25,7 @@ void fused_shape(const za_problem& p, int* gx, int* gy) {
     res = f32 ? (int)FuWaves<float, WV_Z1, 3>::value
               : r == 3 ? (int)FuWaves<double, WV_Z1, 3>::value
                        : r == 2 ? (int)FuWaves<double, WV_Z1, 2>::value : (int)FuWaves<double, WV_Z1, 5>::value;
-  const int strips = (p.nx + FU_COLS - 1) / FU_COLS, cus = 256;
+  const int strips = (p.nx + FU_COLS - 1) / FU_COLS;
   double best = -1;
   // (bands of more than 256 steps only where the grid would have too many)
   for (long long s = 1;; s = s < 256 ? s + 1 : 2 * s) {

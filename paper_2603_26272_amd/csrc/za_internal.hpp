@@ -13,6 +13,7 @@ struct za_ctx {
   za_problem prob;
   int m = 1;
   int device = 0;
+  int cus = 256;             // compute units of the device
   hipStream_t stream = nullptr;
   za::Geom geom;
   za::Phys ph;
@@ -115,19 +116,23 @@ void launch_x_general(za_ctx* c, int mode, const za::SweepArgs& a);
 void launch_y_general(za_ctx* c, int mode, const za::SweepArgs& a);
 int general_y_blocks_per_cu(const za_problem& p);
 
-// Resident 1D kernels (za_line.hip): the launch shape for p (0 blocks: none),
+// Compute units of a device (256 if it cannot be asked).
+int device_cus(int device);
+
+// Resident 1D kernels (za_line.hip): the launch shape for p on a device of
+// this many CUs (0 blocks: none),
 // the device bytes of its exchange words and their reset; up to n steps from
 // *init (one block; nullptr: from the control block), and a right-hand side
 // (one block).
-void line_shape(const za_problem& p, int* blocks, int* waves);
+void line_shape(const za_problem& p, int cus, int* blocks, int* waves);
 size_t line_bytes(int blocks);
 void line_init(za_ctx* c);
 void launch_line(za_ctx* c, double* q, int64_t n, const za::DevCtl* init);
 void launch_line_rhs(za_ctx* c, const double* q, double* rhs);
 
-// Fused 2D Euler stage (za_fused.hip): launch shape for p (gx = 0: none), and
-// a launch (MODE_STAGE or MODE_RHS).
-void fused_shape(const za_problem& p, int* gx, int* gy);
+// Fused 2D Euler stage (za_fused.hip): launch shape for p on a device of this
+// many CUs (gx = 0: none), and a launch (MODE_STAGE or MODE_RHS).
+void fused_shape(const za_problem& p, int cus, int* gx, int* gy);
 void launch_fused(za_ctx* c, int mode, za::SweepArgs a);
 void launch_fused_square(za_ctx* c, int mode, const za::SweepArgs& a);
 void launch_fused_general(za_ctx* c, int mode, const za::SweepArgs& a);

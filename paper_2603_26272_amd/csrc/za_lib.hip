@@ -105,7 +105,7 @@ size_t za_workspace_bytes(const za_problem* p) {
   if (p->dim == 2) b += st;               // the partial stage (counted for fused stages too)
   b += kPartBytes + kRowsBytes;            // partial sums, wave-speed rows, control blocks
   int lb, lw;
-  line_shape(*p, &lb, &lw);
+  line_shape(*p, 256, &lb, &lw);          // (fewer CUs only take fewer lines)
   b += line_bytes(lb);                    // exchange words of the resident 1D kernel
   return b;
 }
@@ -221,23 +221,27 @@ SweepArgs base_args(za_ctx* c) {
   return a;
 }
 
+int device_cus(int device) {
+  int n = 0;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && n > 0) return n;
+  (void)hipGetLastError();
+  return 256;
+}
+
 // Rows per y-sweep block: split each 64-column strip into as many tiles as
 // there are resident block slots per strip, so that one round of blocks
 // covers the grid (no tail round at partial occupancy).
 static int pick_ytile(za_ctx* c) {
   const za_problem& p = c->prob;
   if (p.dim != 2) return 64;
-  int cus = 0;
   int blocks_per_cu = c->fu_gx && !p.pp_limiter ? 3   // (flux output only)
                       : order_of(p) != 3    ? order_y_blocks_per_cu(p)
                       : !general_weights(p) ? y_blocks_per_cu_wv<WV_Z1>(p)
                       : square_powers(p)    ? square_y_blocks_per_cu(p)
                                             : general_y_blocks_per_cu(p);
   if (blocks_per_cu < 1) blocks_per_cu = 2;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus < 1)
-    cus = 256;
   const long long strips = (p.nx + 63) / 64;
-  const long long slots = (long long)blocks_per_cu * cus;
+  const long long slots = (long long)blocks_per_cu * c->cus;
   long long tiles = std::max<long long>(1, slots / strips);
   // a tile of R rows computes R + 1 interface rows, YS_ROWS per step: take
   // the largest R with as many steps as the rows a tile needs
@@ -259,14 +263,12 @@ static int pick_xl_chunks(za_ctx* c) {
     const int v = std::atoi(e);
     return v < 0 ? 0 : std::min(v, 256);
   }
-  int blocks_per_cu = 0, cus = 0;
+  int blocks_per_cu = 0;
   const void* fn = p.system != ZA_EULER ? reinterpret_cast<const void*>(&k_sweep_xl<SYS_ADV, 1, WV_Z1, MODE_LX>)
                                         : reinterpret_cast<const void*>(&k_sweep_xl<SYS_EULER, 3, WV_Z1, MODE_STAGE>);
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks_per_cu, fn, 256, 0) != hipSuccess || blocks_per_cu < 1)
     blocks_per_cu = 3;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus < 1)
-    cus = 256;
-  const long long slots = 4LL * blocks_per_cu * cus;
+  const long long slots = 4LL * blocks_per_cu * c->cus;
   int best = 1;
   long long best_cost = -1;
   for (int nc = 1; nc <= 64; ++nc) {
@@ -482,6 +484,7 @@ void init_shape(za_ctx* c, const za_problem* p, hipStream_t stream) {
   c->m = ncomp_of(*p);
   c->stream = stream;
   (void)hipGetDevice(&c->device);
+  c->cus = device_cus(c->device);
   const size_t ncell = (size_t)p->nx * p->ny;
   c->geom.nx = p->nx;
   c->geom.ny = p->ny;
@@ -503,7 +506,7 @@ void init_shape(za_ctx* c, const za_problem* p, hipStream_t stream) {
   // stand-alone wave-speed pass: at most one block per CU
   c->red_threads = ncell <= 65536 ? 256 : 1024;
   c->red_blocks = (int)std::min<size_t>(SP_ROWS, (ncell + c->red_threads - 1) / c->red_threads);
-  fused_shape(*p, &c->fu_gx, &c->fu_gy);
+  fused_shape(*p, c->cus, &c->fu_gx, &c->fu_gy);
   c->ytile = pick_ytile(c);
   c->xl_chunks = pick_xl_chunks(c);
   // ZA_STEP_GRAPHS=0 runs the steps of za_solve as direct launches instead
@@ -512,7 +515,7 @@ void init_shape(za_ctx* c, const za_problem* p, hipStream_t stream) {
   // 1D problems that fit stay resident for many steps; ZA_RESIDENT=0, or
   // either variable that selects a form of the step launches, turns that off
   // (results are identical).  ZA_LINE_SPIN: the wait limit in clock ticks.
-  line_shape(*p, &c->line_blocks, &c->line_waves);
+  line_shape(*p, c->cus, &c->line_blocks, &c->line_waves);
   const char* e = std::getenv("ZA_RESIDENT");
   if ((e && std::atoi(e) == 0) || std::getenv("ZA_XL_CHUNKS") || std::getenv("ZA_STEP_GRAPHS")) c->line_blocks = 0;
   if ((e = std::getenv("ZA_LINE_SPIN"))) c->line_spin = std::atoll(e);

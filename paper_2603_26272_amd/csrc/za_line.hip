@@ -96,7 +96,7 @@ __global__ void k_words_clear(unsigned long long* w, int n) {
 
 }  // namespace
 
-void line_shape(const za_problem& p, int* blocks, int* waves) {
+void line_shape(const za_problem& p, int cus, int* blocks, int* waves) {
   *blocks = *waves = 0;
   MaxThreads mt;
   if (!line_dispatch(p, mt)) return;
@@ -115,8 +115,9 @@ void line_shape(const za_problem& p, int* blocks, int* waves) {
   for (int w = std::min(4, max_waves); w <= max_waves; w *= 2) {
     const int cells = 64 * w - 1;
     const long long n = ((long long)p.nx + cells - 1) / cells;
-    // a quarter of the wavefronts that 256 CUs hold at the kernel's registers
-    if (n <= LINE_MAX_BLOCKS && n * w <= 64 * max_waves) {
+    // a quarter of the wavefronts that the CUs hold at the kernel's registers:
+    // the blocks wait for each other, so all have to be resident at once
+    if (n <= LINE_MAX_BLOCKS && 4 * n * w <= (long long)cus * max_waves) {
       *blocks = (int)n;
       *waves = w;
       return;

@@ -43,8 +43,8 @@ struct LineArgs {
 };
 
 // Four such launches at once (one per hardware queue) still fit the chip: the
-// host takes at most a quarter of the wavefronts that 256 CUs hold at the
-// kernel's registers (512 of 8 per CU, or 1024 of 16).
+// host takes at most a quarter of the wavefronts that the device's CUs hold
+// at the kernel's registers (of 256 CUs: 512 of 8 per CU, or 1024 of 16).
 constexpr int LINE_MAX_BLOCKS = 128;
 // Up to this many blocks every wavefront publishes its own maxima (one thread
 // waits for each); beyond, the block's are reduced first, one barrier more.

@@ -294,6 +294,7 @@ struct za_server {
   size_t budget = 0;
   int max_slots = 0;
   int device = 0;
+  int cus = 256;
   char* pool_base = nullptr;
   Pool pool;
   Class cls[NCLASS];
@@ -334,28 +335,28 @@ static int serve_xl_chunks(const za_problem& p) {
 }
 
 // Bands of a 2D request, fixed at admission: of up to SERVE_STEPS steps, as
-// tall as leave the request a block per CU (its latency when alone; taller
+// tall as leave the request a block per CU of the device (its latency when alone; taller
 // ones in larger batches changed nothing).  ZA_SRV_YTILE in the environment
 // forces the rows of a band (rounded to a whole number of steps, at least
 // one).
-static int serve_bands(const za_problem& p, int strips) {
+static int serve_bands(const za_problem& p, int strips, int cus) {
   int s = SERVE_STEPS;
   if (const char* e = std::getenv("ZA_SRV_YTILE")) {
     s = std::min(std::max(1, std::atoi(e) / FU_NW), 256);
   } else {
-    while (s > 1 && (long long)strips * ((p.ny + FU_NW * s - 2) / (FU_NW * s - 1)) < 256) --s;
+    while (s > 1 && (long long)strips * ((p.ny + FU_NW * s - 2) / (FU_NW * s - 1)) < cus) --s;
   }
   return (p.ny + FU_NW * s - 2) / (FU_NW * s - 1);
 }
 
 // The launch shape of a request, and its device bytes in the pool.
-static size_t footprint(const za_problem& p, SlotDesc* d) {
+static size_t footprint(const za_problem& p, int cus, SlotDesc* d) {
   const size_t S = (size_t)ncomp(p) * p.nx * p.ny * sizeof(double);
   d->xl_chunks = serve_xl_chunks(p);
   d->strips = d->bands = 0;
   if (p.dim == 2) {
     d->strips = (p.nx + FU_COLS - 1) / FU_COLS;
-    d->bands = serve_bands(p, d->strips);
+    d->bands = serve_bands(p, d->strips, cus);
     d->blocks = d->strips * d->bands;
   } else {
     const long long w = d->xl_chunks > 0 ? xl_waves(p.nx, p.ny, d->xl_chunks)
@@ -481,7 +482,7 @@ static void admit(za_server* sv) {
     if (C.free_slots.empty()) { ++it; continue; }
     SlotDesc& d = r->desc;
     std::memset(&d, 0, sizeof(d));
-    const size_t need = footprint(r->prob, &d);
+    const size_t need = footprint(r->prob, sv->cus, &d);
     size_t off;
     if (!sv->pool.alloc(need, &off)) { ++it; continue; }
     r->off = off;
@@ -760,6 +761,7 @@ za_status za_server_create(size_t hbm_budget_bytes, int32_t max_slots, int32_t d
   sv->budget = hbm_budget_bytes;
   sv->max_slots = max_slots;
   sv->device = device;
+  sv->cus = device_cus(device);
   if (const char* e = std::getenv("ZA_SRV_FAIL_BURST")) sv->fail_burst = std::atoll(e);
   if (const char* e = std::getenv("ZA_SRV_FAIL_XFER")) sv->fail_xfer = std::atoll(e);
   if (const char* e = std::getenv("ZA_SRV_GRAPHS")) sv->graphs = std::atoi(e) != 0;
@@ -832,7 +834,7 @@ za_status za_server_submit(za_server* sv, const za_problem* p, const double* q0,
   if (p->system != ZA_EULER || general_weights(*p) || order_of(*p) != 3 || p->pp_limiter)
     return ZA_ERR_UNSUPPORTED;
   SlotDesc shape;
-  if (footprint(*p, &shape) > sv->budget) return ZA_ERR_NOMEM;
+  if (footprint(*p, sv->cus, &shape) > sv->budget) return ZA_ERR_NOMEM;
   auto r = std::make_unique<Req>();
   r->prob = *p;
   r->cls = class_of(*p);

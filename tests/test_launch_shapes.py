@@ -1,0 +1,47 @@
+"""Launch shapes chosen on the host (no GPU): the resident 1D lines, whose
+blocks wait for each other, and the fused 2D Euler stage follow the number of
+compute units they are given."""
+import ctypes as C
+
+import pytest
+
+from paper_2603_26272_amd import za
+from paper_2603_26272_amd.problem import ADVECTION, EULER, Problem
+
+ARGS = "RK10za_problemiPiS2_"
+
+
+def _shape(name, P, cus):
+    f = getattr(C.CDLL(za.LIB_PATH), f"_Z{len(name)}{name}{ARGS}")
+    f.restype = None
+    a, b = C.c_int(-1), C.c_int(-1)
+    f(C.byref(za.ZaProblem.from_problem(P)), C.c_int(cus), C.byref(a), C.byref(b))
+    return a.value, b.value
+
+
+@pytest.mark.parametrize("cus", [8, 32, 64, 128, 256, 304])
+@pytest.mark.parametrize("system,waves_per_cu", [(EULER, 8), (ADVECTION, 16)])
+def test_lines_take_at_most_a_quarter_of_the_device(cus, system, waves_per_cu):
+    """Four lines at once (one per hardware queue) have all their blocks
+    resident: a line of several blocks takes a quarter of the wavefronts."""
+    several = 0
+    for N in (64, 500, 600, 1021, 1500, 4096, 5000, 16321, 32640, 32704, 65472):
+        blocks, waves = _shape("line_shape", Problem(dim=1, system=system, nx=N), cus)
+        if blocks > 1:
+            assert 4 * blocks * waves <= cus * waves_per_cu, (N, blocks, waves)
+            assert blocks * (64 * waves - 1) >= N
+            several += 1
+    assert several > 0 or cus < 16
+
+
+def test_line_of_one_block_needs_one_cu():
+    assert _shape("line_shape", Problem(dim=1, nx=200), 1) == (1, 4)
+
+
+def test_fused_bands_follow_the_device():
+    """128^2: 3 strips; bands of one step (3 rows) while every block finds a
+    CU of its own, taller ones on a device that would take rounds of them."""
+    P = Problem(dim=2, nx=128, ny=128)
+    assert _shape("fused_shape", P, 256) == (3, 43)
+    gx, gy = _shape("fused_shape", P, 16)
+    assert gx == 3 and gx * gy <= 3 * 16
