@@ -4,6 +4,23 @@
 
 using namespace za;
 
+// The value of the kernel that p launches, by the conditions of launch_fused.
+template <class T, int R>
+static int fused_waves_t(const za_problem& p) {
+  return !general_weights(p) ? FuWaves<T, WV_Z1, R>::value
+         : square_powers(p)  ? FuWaves<T, WV_SQUARE, R>::value
+                             : FuWaves<T, WV_GENERAL, R>::value;
+}
+int fused_waves(const za_problem& p) {
+  if (p.precision == ZA_FP32_RECON) return fused_waves_t<float, 3>(p);
+  switch (order_of(p)) {
+    case 2: return fused_waves_t<double, 2>(p);
+    case 3: return fused_waves_t<double, 3>(p);
+    case 4: return fused_waves_t<double, 4>(p);
+    default: return fused_waves_t<double, 5>(p);
+  }
+}
+
 // Strips and bands: the band height that minimises the longest CU's work,
 // counted in steps of one wavefront per SIMD.  A block of s steps covers
 // 4 s - 1 rows.  n resident blocks per CU take n s steps of a CU's issue
@@ -15,16 +32,7 @@ using namespace za;
 void fused_shape(const za_problem& p, int cus, int* gx, int* gy) {
   *gx = *gy = 0;
   if (p.dim != 2 || p.system != ZA_EULER) return;
-  const bool f32 = p.precision == ZA_FP32_RECON;
-  const int r = order_of(p);
-  int res;
-  if (general_weights(p))
-    res = square_powers(p) ? (f32 ? (int)FuWaves<float, WV_SQUARE, 3>::value : (int)FuWaves<double, WV_SQUARE, 3>::value)
-                           : (f32 ? (int)FuWaves<float, WV_GENERAL, 3>::value : (int)FuWaves<double, WV_GENERAL, 3>::value);
-  else
-    res = f32 ? (int)FuWaves<float, WV_Z1, 3>::value
-              : r == 3 ? (int)FuWaves<double, WV_Z1, 3>::value
-                       : r == 2 ? (int)FuWaves<double, WV_Z1, 2>::value : (int)FuWaves<double, WV_Z1, 5>::value;
+  const int res = fused_waves(p);   // resident blocks per CU of the kernel that p launches
   const int strips = (p.nx + FU_COLS - 1) / FU_COLS;
   double best = -1;
   // (bands of more than 256 steps only where the grid would have too many)

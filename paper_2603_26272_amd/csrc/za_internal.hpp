@@ -130,8 +130,10 @@ void line_init(za_ctx* c);
 void launch_line(za_ctx* c, double* q, int64_t n, const za::DevCtl* init);
 void launch_line_rhs(za_ctx* c, const double* q, double* rhs);
 
-// Fused 2D Euler stage (za_fused.hip): launch shape for p on a device of this
-// many CUs (gx = 0: none), and a launch (MODE_STAGE or MODE_RHS).
+// Fused 2D Euler stage (za_fused.hip): blocks per CU that the kernel for p is
+// compiled for, launch shape for p on a device of this many CUs (gx = 0:
+// none), and a launch (MODE_STAGE or MODE_RHS).
+int fused_waves(const za_problem& p);
 void fused_shape(const za_problem& p, int cus, int* gx, int* gy);
 void launch_fused(za_ctx* c, int mode, za::SweepArgs a);
 void launch_fused_square(za_ctx* c, int mode, const za::SweepArgs& a);

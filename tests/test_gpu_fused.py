@@ -85,3 +85,27 @@ def test_bands_do_not_change_the_result():
             assert np.array_equal(got, np.tile(one, (1, k, 1)))
         else:
             assert_close(got, np.tile(one, (1, k, 1)), 1e-12, f"{k} tiles")
+
+
+@pytest.mark.parametrize("order", [4, 5])
+def test_wide_squared_kernels_agree_bitwise(order):
+    """Squared weights at r = 4, 5 run one kernel where every block has a CU
+    of its own and another where blocks share CUs (more registers against
+    more blocks): a periodic tile gives the same bits through either."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_26272_amd.za import Context
+    P, q0 = _data(128, 32)
+    P = P.with_(bc_x=PERIODIC, bc_y=PERIODIC, order=order, weight_L=0.0, p=2.0)
+    k = 64                                   # 33 blocks, then more than one per CU
+    Pk = P.with_(ny=32 * k, yhi=P.yhi * k)
+    assert Pk.dy == P.dy
+    out = []
+    for Pi, qi in ((P, q0), (Pk, np.tile(q0, (1, k, 1)))):
+        q = torch.from_numpy(qi).cuda()
+        with Context(Pi) as ctx:
+            rhs = ctx.rhs(q).cpu().numpy()
+            ctx.solve(q, 0.0, 3)
+        out.append((rhs, q.cpu().numpy()))
+    for a, b in zip(*out):
+        assert np.array_equal(np.tile(a, (1, k, 1)), b)

@@ -45,3 +45,40 @@ def test_fused_bands_follow_the_device():
     assert _shape("fused_shape", P, 256) == (3, 43)
     gx, gy = _shape("fused_shape", P, 16)
     assert gx == 3 and gx * gy <= 3 * 16
+
+
+def _model(P, res, cus=256):
+    """The cost rule of fused_shape for `res` resident blocks per CU."""
+    strips, best = -(-P.nx // 63), None
+    for s in range(1, 257):
+        nb = -(-P.ny // (4 * s - 1))
+        m = -(-strips * nb // cus)
+        full, rest = divmod(m, res)
+        idle = 1.5 if rest == 1 else (1.15 if rest == 2 and res > 2 else 1.0)
+        cost = full * (res * s + 2.0) + (idle * rest * s + 2.0 if rest else 0.0)
+        if best is None or cost < best[0]:
+            best = (cost, strips, nb)
+        if m <= 1:
+            break
+    return best[1:]
+
+
+JS = dict(weight_L=0.0, p=2.0)
+F32 = dict(precision=1, eps=1e-20, mu0=1e-8)
+
+
+@pytest.mark.parametrize("n", [64, 300, 512, 700, 1024, 2048])
+@pytest.mark.parametrize("kind,res", [(dict(), 3), (dict(order=2), 3), (dict(order=4), 2), (dict(order=5), 2),
+                                      (JS, 2), (dict(order=2, **JS), 2), (dict(order=4, **JS), 2),
+                                      (dict(order=5, **JS), 2), (F32, 4), (dict(**F32, **JS), 3)])
+def test_fused_bands_use_the_kernels_own_occupancy(kind, res, n):
+    """The bands are those for as many resident blocks per CU as the kernel
+    of these weights, this order and this precision is launched for."""
+    P = Problem(dim=2, nx=n, ny=n, **kind)
+    assert _shape("fused_shape", P, 256) == _model(P, res)
+    assert _waves(P) == res
+
+
+def _waves(P):
+    f = getattr(C.CDLL(za.LIB_PATH), "_Z11fused_wavesRK10za_problem")
+    return f(C.byref(za.ZaProblem.from_problem(P)))
