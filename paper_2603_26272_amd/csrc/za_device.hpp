@@ -98,11 +98,21 @@ __device__ __forceinline__ void sqrt_rsq(float x, float& s, float& h) {
 // omega_k, and so does bmin^(-pq) (bmin the smallest b of the stencil), so the
 // weight is taken as (bmin / b)^(pq) <= 1, defined where tau = 0 and free of
 // overflow.  Outside WV_GENERAL this is the paper's 1 + tau / b.
+//
+// FP64 pow() is called, not inlined: with the 64 copies of a fused r = 3 stage
+// that kernel is 302 KB of code, far beyond the 64 KB instruction cache, and
+// takes 256 registers with 30 spilled; with calls 47 + 1.7 KB, 246 and none.
+// p = 3/2, us a stage, inlined -> called: 2048^2 r = 2 1590 -> 1447, r = 3
+// 2204 -> 2055, r = 5 4125 -> 3529; 128^2 r = 3 57 -> 53.  FP32 pow() is
+// better inlined (1024^2 297 us, called 309).
+__device__ __attribute__((noinline)) inline double pow_call(double x, double e) { return pow(x, e); }
+__device__ __forceinline__ float pow_call(float x, float e) { return pow(x, e); }
+
 template <class T, int WV>
 __device__ __forceinline__ T z_pow(T x, T e) {
   if (e == T(1)) return x;
   if constexpr (WV == WV_SQUARE) return x * x;
-  else return pow(x, e);
+  else return pow_call(x, e);
 }
 
 template <class T, int WV>

@@ -13,11 +13,14 @@ namespace za {
 // where blocks share CUs (us a stage, two against one: r = 4, 512^2 61 / 70,
 // 2048^2 597 / 881; r = 5 99 / 97 and 1098 / 1229) and loses where none do
 // (128^2: r = 4 21.5 / 20.2, r = 5 30.3 / 26.3): `alone` is the value for
-// launches of at most one block per CU.  pow() takes one.
+// launches of at most one block per CU.  Weights with pow() (p = 3/2, us a
+// stage of 1024^2; two sweeps per stage 403, 749, 938, 1442, FP32 348): r = 2
+// 418 at two, 378 at three, r = 3 868 at one, 558 at two, r = 4 1124, 732,
+// r = 5 1453, 944, FP32 382 at two, 298 at three, 357 at four.
 template <class T, int WV, int R>
 struct FuWaves {
   enum { f32 = sizeof(T) == sizeof(float),
-         value = WV == WV_GENERAL ? (f32 ? 2 : 1)
+         value = WV == WV_GENERAL ? (f32 || R == 2 ? 3 : 2)
                  : WV == WV_SQUARE ? (f32 ? 3 : 2)
                                    : (R == 3 ? (f32 ? 4 : 3) : (R == 2 ? 3 : 2)),
          alone = WV == WV_SQUARE && R > 3 ? 1 : (int)value };

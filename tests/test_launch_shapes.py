@@ -82,3 +82,16 @@ def test_fused_bands_use_the_kernels_own_occupancy(kind, res, n):
 def _waves(P):
     f = getattr(C.CDLL(za.LIB_PATH), "_Z11fused_wavesRK10za_problem")
     return f(C.byref(za.ZaProblem.from_problem(P)))
+
+
+P15 = dict(p=1.5)
+
+
+@pytest.mark.parametrize("kind,res", [(dict(order=2, **P15), 3), (P15, 2), (dict(order=4, **P15), 2),
+                                      (dict(order=5, **P15), 2), (dict(**F32, **P15), 3)])
+def test_pow_kernels_share_the_cu(kind, res):
+    """Weights with pow() leave most issue slots of a CU idle with one block:
+    the fused kernels are compiled, and their bands chosen, for several."""
+    P = Problem(dim=2, nx=512, ny=512, **kind)
+    assert _waves(P) == res
+    assert _shape("fused_shape", P, 256) == _model(P, res)
