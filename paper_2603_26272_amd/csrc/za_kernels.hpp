@@ -1200,16 +1200,11 @@ __device__ __forceinline__ void sweep_y_tile(const SweepArgs& a, const CfgArg<T>
 // band by of the ceil(ny / ytile) bands of (near) equal height.
 template <int SYS, int M, class T, int MODE, int WV, int R = 3, int PP = 0>
 __device__ __forceinline__ void sweep_y_body(const SweepArgs& a, const CfgArg<T>& cfg, int bx, int by, int gx) {
-  SweepConst sk;
-  if (MODE != MODE_STAGE && a.sp_in) {   // a right-hand side or fluxes: no control block
-    SweepConst kx;
-    StageLoads<SYS, 2> sl;
-    stage_load(a, sl);
-    (void)stage_begin(a, sl, -1, 2, kx, sk);
-  } else {
-    if (a.check_run && !gptr(a.ctl)->run) return;
-    sk = sweep_const<1>(a.ctl, a.g, PP && SYS == SYS_EULER && MODE == MODE_STAGE, true);
-  }
+  // The x-sweep (or the launch ahead of it) has left both directions' constants
+  // in the control block.  (Reducing the rows here again cost the fluxes of
+  // p = 3/2 weights a wavefront per SIMD: 256 + 12 registers, 252 without.)
+  if (a.check_run && !gptr(a.ctl)->run) return;
+  const SweepConst sk = sweep_const<1>(a.ctl, a.g, PP && SYS == SYS_EULER && MODE == MODE_STAGE, true);
   double rs[NPART];
 #pragma unroll
   for (int t = 0; t < NPART; ++t) rs[t] = -__builtin_huge_val();

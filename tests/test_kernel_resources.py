@@ -1,0 +1,70 @@
+"""Registers and scratch memory of the kernels in the built library, read from
+the metadata that the compiler leaves in its code objects (no GPU): the
+occupancy that the launch shapes and the comments state."""
+import struct
+import subprocess
+
+import pytest
+
+msgpack = pytest.importorskip("msgpack")
+
+from paper_2603_26272_amd import za
+
+
+def _notes(elf):
+    """The AMDGPU metadata (note type 32) of one ELF code object."""
+    shoff, = struct.unpack_from("<Q", elf, 0x28)
+    entsize, num = struct.unpack_from("<HH", elf, 0x3A)
+    for k in range(num):
+        sh = shoff + k * entsize
+        kind, = struct.unpack_from("<I", elf, sh + 4)
+        off, size = struct.unpack_from("<QQ", elf, sh + 24)
+        o = off
+        while kind == 7 and o < off + size:   # SHT_NOTE
+            nsz, dsz, t = struct.unpack_from("<III", elf, o)
+            d = o + 12 + (nsz + 3) // 4 * 4
+            if t == 32:
+                yield msgpack.unpackb(elf[d:d + dsz])
+            o = d + (dsz + 3) // 4 * 4
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    """{demangled name: metadata}"""
+    blob = open(za.LIB_PATH, "rb").read()
+    found, i = {}, blob.find(b"__CLANG_OFFLOAD_BUNDLE__")
+    while i >= 0:
+        n, = struct.unpack_from("<Q", blob, i + 24)
+        o = i + 32
+        for _ in range(n):
+            off, size, ln = struct.unpack_from("<QQQ", blob, o)
+            name = blob[o + 24:o + 24 + ln]
+            o += 24 + ln
+            if b"gfx950" in name and size:
+                for note in _notes(blob[i + off:i + off + size]):
+                    found.update({k[".name"]: k for k in note["amdhsa.kernels"]})
+        i = blob.find(b"__CLANG_OFFLOAD_BUNDLE__", i + 24)
+    names = subprocess.run(["c++filt"], input="\n".join(found), capture_output=True, text=True, check=True).stdout
+    out = {d: k for d, k in zip(names.splitlines(), found.values())}
+    assert len(out) > 200
+    return out
+
+
+def _waves(k):
+    """Wavefronts per SIMD that the registers (vector and accumulation
+    together, in units of 8 of 512) allow."""
+    return min(8, 512 // (-(-k[".vgpr_count"] // 8) * 8))
+
+
+def _only(kernels, part):
+    hits = [k for n, k in kernels.items() if part in n]
+    assert hits, part
+    return hits
+
+
+# (weights: 1 with pow(), 2 powers of 1 and 2; r)
+@pytest.mark.parametrize("wv,r", [(1, 2), (1, 3), (2, 3), (2, 4)])
+@pytest.mark.parametrize("d", ["x", "y"])
+def test_flux_sweeps_of_general_weights_hold_two_wavefronts(kernels, d, wv, r):
+    for k in _only(kernels, f"k_sweep_{d}_any<1, 4, double, 0, {wv}, {r}>"):
+        assert _waves(k) >= 2, k[".vgpr_count"]
