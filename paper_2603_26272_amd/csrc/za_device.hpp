@@ -46,7 +46,11 @@ struct WeightCfg {
 // need pow(), which costs more than the rest of the interface (32 calls per
 // Euler interface; JS weights, 2D Euler 512^2, 10 steps: 6.41 ms with pow(),
 // 1.60 ms without).
-enum { WV_Z1 = 0, WV_GENERAL = 1, WV_SQUARE = 2 };
+//
+// WV_INLINE is WV_GENERAL with pow() inlined: scalar laws, whose 8 calls per
+// interface (r = 3) fit the instruction cache (Burgers 2D, p = 3/2, 300^2: 43.8
+// us a stage, 47.2 with calls).
+enum { WV_Z1 = 0, WV_GENERAL = 1, WV_SQUARE = 2, WV_INLINE = 3 };
 
 // The hardware FP64 reciprocal and reciprocal-square-root estimates are
 // good to a relative 2^-24 (measured over 4M normal operands on gfx950: at
@@ -106,13 +110,13 @@ __device__ __forceinline__ void sqrt_rsq(float x, float& s, float& h) {
 // 2204 -> 2055, r = 5 4125 -> 3529; 128^2 r = 3 57 -> 53.  FP32 pow() is
 // better inlined (1024^2 297 us, called 309).
 __device__ __attribute__((noinline)) inline double pow_call(double x, double e) { return pow(x, e); }
-__device__ __forceinline__ float pow_call(float x, float e) { return pow(x, e); }
 
 template <class T, int WV>
 __device__ __forceinline__ T z_pow(T x, T e) {
   if (e == T(1)) return x;
   if constexpr (WV == WV_SQUARE) return x * x;
-  else return pow_call(x, e);
+  else if constexpr (WV == WV_GENERAL && sizeof(T) == sizeof(double)) return pow_call(x, e);
+  else return pow(x, e);
 }
 
 template <class T, int WV>

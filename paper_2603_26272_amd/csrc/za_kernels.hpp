@@ -434,7 +434,7 @@ __device__ __forceinline__ void stencil_flux(const T* __restrict__ rec, int fs, 
       w[j] = rec[off[j]];
       g[j] = rec[fs + off[j]];
     }
-    Fh[0] = split_pair<T, WV, R>(w, g, (T)sk.al[0], cfg);
+    Fh[0] = split_pair<T, (WV == WV_GENERAL ? (int)WV_INLINE : WV), R>(w, g, (T)sk.al[0], cfg);
   }
 }
 
@@ -1245,7 +1245,8 @@ template <int MODE, int WV>
 __global__ __launch_bounds__(256) void k_sweep_y_pp(SweepArgs a, CfgArg<double> cfg) {
   sweep_y_body<SYS_EULER, 4, double, MODE, WV, 3, 1>(a, cfg, blockIdx.x, blockIdx.y, gridDim.x);
 }
-// Other orders with Z weights: an occupancy target per stencil width.
+// Other orders with Z weights, and 1D Euler weights with pow(): an occupancy
+// target per stencil width.
 template <int SYS, int M, class T, int MODE, int WV, int R, int WAVES>
 __global__ __launch_bounds__(256, WAVES) void k_sweep_x_r(SweepArgs a, CfgArg<T> cfg) {
   sweep_x_body<SYS, M, T, MODE, WV, R>(a, cfg, blockIdx.x);

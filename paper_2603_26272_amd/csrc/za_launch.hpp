@@ -49,6 +49,13 @@ static void launch_x_t(za_ctx* c, int mode, SweepArgs a) {
         hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_STAGE, WV>), grid, blk, 0, c->stream, a, cfg);
       else if constexpr (SYS != SYS_EULER)
         hipLaunchKernelGGL((k_sweep_x<SYS, M, T, MODE_LX, WV>), grid, blk, 0, c->stream, a, cfg);
+    } else if constexpr (SYS == SYS_EULER && WV == WV_GENERAL && sizeof(T) == sizeof(double)) {
+      // three wavefronts per SIMD: 170 registers where 168 give them (line of
+      // 4e6 cells, p = 3/2: 679 us a stage, 760 with two)
+      if (mode == MODE_RHS)
+        hipLaunchKernelGGL((k_sweep_x_r<SYS, M, T, MODE_RHS, WV, 3, 3>), grid, blk, 0, c->stream, a, cfg);
+      else
+        hipLaunchKernelGGL((k_sweep_x_r<SYS, M, T, MODE_STAGE, WV, 3, 3>), grid, blk, 0, c->stream, a, cfg);
     } else {
       if (mode == MODE_RHS)
         hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_RHS, WV>), grid, blk, 0, c->stream, a, cfg);

@@ -25,7 +25,12 @@ void x_any(za_ctx* c, int mode, const SweepArgs& a, const CfgArg<double>& cfg, d
     hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_FLUX, WV, R>), grid, dim3(256), 0, c->stream, a, cfg);
     return;
   }
-  if constexpr (M != 4) switch (mode) {
+  if constexpr (SYS == SYS_EULER && M == 3 && R == 2 && WV == WV_GENERAL) {   // 130 registers, 128 give four
+    if (mode == MODE_RHS)
+      hipLaunchKernelGGL((k_sweep_x_r<SYS, M, double, MODE_RHS, WV, R, 4>), grid, dim3(256), 0, c->stream, a, cfg);
+    else
+      hipLaunchKernelGGL((k_sweep_x_r<SYS, M, double, MODE_STAGE, WV, R, 4>), grid, dim3(256), 0, c->stream, a, cfg);
+  } else if constexpr (M != 4) switch (mode) {
     case MODE_RHS: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_RHS, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
     case MODE_LX: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_LX, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;
     default: hipLaunchKernelGGL((k_sweep_x_any<SYS, M, double, MODE_STAGE, WV, R>), grid, dim3(256), 0, c->stream, a, cfg); break;

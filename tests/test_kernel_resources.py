@@ -68,3 +68,14 @@ def _only(kernels, part):
 def test_flux_sweeps_of_general_weights_hold_two_wavefronts(kernels, d, wv, r):
     for k in _only(kernels, f"k_sweep_{d}_any<1, 4, double, 0, {wv}, {r}>"):
         assert _waves(k) >= 2, k[".vgpr_count"]
+
+
+@pytest.mark.parametrize("r,waves", [(2, 4), (3, 3)])
+@pytest.mark.parametrize("mode", [1, 3])   # right-hand side, stage
+def test_1d_euler_sweeps_of_pow_weights_keep_their_wavefronts(kernels, mode, r, waves):
+    """Two registers more would cost one (a line of 4e6 cells at p = 3/2:
+    12 % of a stage)."""
+    hits = [k for n, k in kernels.items() if f"k_sweep_x_r<1, 3, double, {mode}, 1, {r}, " in n]
+    assert hits
+    for k in hits:
+        assert _waves(k) >= waves and k[".private_segment_fixed_size"] == 0, k[".vgpr_count"]
