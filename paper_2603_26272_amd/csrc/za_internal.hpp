@@ -32,7 +32,6 @@ struct za_ctx {
   hipStream_t capture_stream = nullptr;
   hipGraphExec_t graph_exec = nullptr;  // GRAPH_STEPS steps for state graph_q
   const double* graph_q = nullptr;
-  int chunk_steps = 0;       // steps per host check in za_solve (0: default)
   // resident 1D kernels (za_line.hpp): blocks and wavefronts per block (0:
   // not for this problem), exchange words, the next launch's first tag, and
   // the wait limit (< 0: default)

@@ -448,33 +448,47 @@ static za_status read_ctl(za_ctx* c, DevCtl* h) {
 // timing brackets the launches of single kernels instead).
 static bool line_ready(const za_ctx* c) { return c->line_blocks > 0 && c->line_ok && !c->timing; }
 
-// n RK3 steps from the control block (start: from this one instead); with
-// read, *h receives the control block afterwards.  A resident launch of
-// several blocks needs *h to hold the control block before the steps (or
-// start), to go back to if a block waits too long for the others (another
-// kernel kept one from being scheduled): the steps are then repeated, and the
-// context stays with, ordinary launches.
-static za_status advance(za_ctx* c, double* q, int64_t n, const DevCtl* start, bool read, DevCtl* h) {
+// Steps between host checks: a resident launch retires steps beyond the end
+// by itself and costs nothing extra per step; ordinary launches go on for
+// nothing until the host has looked (64 times as long between checks where
+// only an inadmissible state ends the steps early).
+static int64_t steps_per_check(const za_ctx* c, bool equal_steps) {
+  if (line_ready(c)) return 4096;
+  return equal_steps ? 64 * 32 : 32;
+}
+
+// The next of at most n RK3 steps (those until the next host check; returned
+// in *n) from the control block (start: from this one instead).  *h receives
+// the control block afterwards, but if these are all n steps and !read_last.
+// A resident launch of several blocks needs *h to hold the control block
+// before the steps (or start), to go back to if a block waits too long for
+// the others (another kernel kept one from being scheduled): the context
+// stays with ordinary launches from there.
+static za_status advance(za_ctx* c, double* q, int64_t* n, bool equal_steps, const DevCtl* start, bool read_last,
+                         DevCtl* h) {
   za_status st;
+  const int64_t all = *n;
+  *n = std::min(all, steps_per_check(c, equal_steps));
+  DevCtl before;
   if (line_ready(c) && c->line_blocks == 1) {
-    launch_line(c, q, n, start);
+    launch_line(c, q, *n, start);
     ZA_CHECK_LAUNCH(c, "step launch");
-    return read ? read_ctl(c, h) : ZA_OK;
+    return read_last || *n < all ? read_ctl(c, h) : ZA_OK;
   }
   if (line_ready(c)) {
-    const DevCtl before = start ? *start : *h;
+    before = start ? *start : *h;
     if (start) launch_ctl(c, *start);
-    launch_line(c, q, n, nullptr);
+    launch_line(c, q, *n, nullptr);
     ZA_CHECK_LAUNCH(c, "step launch");
     if ((st = read_ctl(c, h)) != ZA_OK) return st;
     if (!h->stuck) return ZA_OK;
     c->line_ok = false;
     c->speeds_valid = false;
-    if ((st = enqueue_steps(c, q, n, &before)) != ZA_OK) return st;
-  } else if ((st = enqueue_steps(c, q, n, start)) != ZA_OK) {
-    return st;
+    start = &before;
+    *n = std::min(all, steps_per_check(c, equal_steps));
   }
-  return read ? read_ctl(c, h) : ZA_OK;
+  if ((st = enqueue_steps(c, q, *n, start)) != ZA_OK) return st;
+  return read_last || *n < all ? read_ctl(c, h) : ZA_OK;
 }
 
 // Everything a context derives from its problem without allocating: the
@@ -674,9 +688,6 @@ za_status za_solve(za_ctx* c, double* q, double t_final, int64_t max_steps, za_s
   const double inf = std::numeric_limits<double>::infinity();
   DevCtl h;
   za_status st;
-  // steps between host checks: a resident launch retires steps beyond the end
-  // by itself and costs nothing extra per step
-  int64_t chunk = c->chunk_steps > 0 ? c->chunk_steps : (line_ready(c) ? 4096 : 32);
   if (t_final > 0.0 && p.dt_rule == ZA_DT_CFL_H2) {
     // fixed dt = cfl h^2: n equal steps, the last one lands on t_final
     const double h2 = p.dim == 2 ? std::min(c->geom.dx, c->geom.dy) : c->geom.dx;
@@ -689,11 +700,10 @@ za_status za_solve(za_ctx* c, double* q, double t_final, int64_t max_steps, za_s
     const DevCtl v = h;
     if (n_equal < 1) launch_ctl(c, v);
     for (int64_t s = 0; s < n_equal;) {
-      const int64_t k = std::min<int64_t>(n_equal - s, line_ready(c) ? chunk : 64 * chunk);
-      const bool more = s + k < n_equal;
-      if ((st = advance(c, q, k, s == 0 ? &v : nullptr, more, &h)) != ZA_OK) return st;
+      int64_t k = n_equal - s;
+      if ((st = advance(c, q, &k, true, s == 0 ? &v : nullptr, false, &h)) != ZA_OK) return st;
       s += k;
-      if (more && h.bad) break;
+      if (s < n_equal && h.bad) break;
     }
     if (n_run == n) {
       const double last = t_final - (double)(n - 1) * dt;
@@ -709,13 +719,11 @@ za_status za_solve(za_ctx* c, double* q, double t_final, int64_t max_steps, za_s
     // enqueues chunks and lets the device retire the steps beyond t_final.
     int64_t enqueued = 0;
     while (true) {
-      int64_t n = chunk;
-      if (t_final <= 0.0) n = std::min<int64_t>(chunk, max_steps - enqueued);
-      if ((st = advance(c, q, n, enqueued == 0 ? &v : nullptr, true, &h)) != ZA_OK) return st;
+      int64_t n = t_final <= 0.0 ? max_steps - enqueued : std::numeric_limits<int64_t>::max();
+      if ((st = advance(c, q, &n, false, enqueued == 0 ? &v : nullptr, true, &h)) != ZA_OK) return st;
       enqueued += n;
       if (!h.active || h.bad) break;
       if (t_final <= 0.0 && enqueued >= max_steps) break;
-      if (!line_ready(c) && chunk > 32 && c->chunk_steps <= 0) chunk = 32;
     }
   }
   if (info) {

@@ -138,3 +138,46 @@ def test_two_streams(monkeypatch):
     [t.start() for t in th]
     [t.join() for t in th]
     assert all(np.array_equal(g, ref) for g in got)
+
+
+def _blow_up(N=1100):
+    """Advection with linear weights and a fixed step just beyond the limit of
+    the scheme: the state overflows after 5819 of 300,000 steps."""
+    x = W.centres(N, -1.0, 1.0)
+    P = Problem(dim=1, system=ADVECTION, nx=N, ny=1, xlo=-1.0, xhi=1.0, bc_x=PERIODIC, linear_weights=1)
+    P = P.with_(dt_rule=1, cfl=1.22 / P.dx)
+    return P, (0.5 + 0.3 * np.sin(np.pi * x + 0.3)).reshape(1, 1, N), 1.22 * P.dx * 300000
+
+
+def test_launches_after_a_long_wait_are_checked_as_often(monkeypatch):
+    """Once the blocks have given up, ordinary launches must stop as soon
+    after the end (or an inadmissible state) as without the resident kernel:
+    32 steps (2048 equal steps) between host checks, not 4096 (262,144)."""
+    import time
+    from paper_2603_26272_amd.za import Context
+    P, q0, T = _blow_up()
+    Pe, qe = _data(EULER, 700)
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+    def seconds(P, q0, T, **env):
+        for k in ("ZA_RESIDENT", "ZA_LINE_SPIN", "ZA_XL_CHUNKS", "ZA_STEP_GRAPHS"):
+            monkeypatch.delenv(k, raising=False)
+        for k, v in env.items():
+            monkeypatch.setenv(k, v)
+        best, res = 1e9, None
+        for _ in range(3):
+            q = torch.from_numpy(np.ascontiguousarray(q0)).cuda()
+            with Context(P) as ctx:
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                res = ctx.solve(q, T, 0, check=False)
+                best = min(best, time.perf_counter() - t)
+        return best, res, q.cpu().numpy()
+
+    # (4096 steps between checks: 31 ms against 0.6 ms for the first of these)
+    for P, q0, T in ((Pe, qe, 20.3 * 0.5 * Pe.dx / 2.5), (P, q0, T)):
+        ref = seconds(P, q0, T, ZA_RESIDENT="0")
+        got = seconds(P, q0, T, ZA_LINE_SPIN="0")
+        assert got[1] == ref[1] and np.array_equal(got[2], ref[2], equal_nan=True)
+        assert got[0] < 4.0 * ref[0], (got[0], ref[0])
