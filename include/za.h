@@ -131,9 +131,10 @@ typedef struct {
  * are fixed here; the environment variable ZA_XL_CHUNKS, read at this call,
  * sets the chunks of 64 interfaces per row segment of the looped x-sweep
  * (1D, and 2D scalar laws; 0: one-shot sweep; results are identical either
- * way).  1D problems of up to some
- * ten thousand cells run their steps in one resident launch; ZA_RESIDENT=0
- * in the environment selects ordinary launches (identical results). */
+ * way).  1D problems of up to some ten thousand cells run their steps in one
+ * resident launch.  In the environment, read at this call, ZA_RESIDENT=0,
+ * ZA_STEP_GRAPHS=0 (steps as direct launches, no captured graphs) and any
+ * ZA_XL_CHUNKS select ordinary launches instead (identical results). */
 za_status za_ctx_create(const za_problem* problem, void* hip_stream, za_ctx** out);
 /* Not from the paper (resource management): synchronise the context's
  * stream, free its workspace and the context.  ZA_ERR_ARG for NULL. */

@@ -115,6 +115,9 @@ void launch_x_general(za_ctx* c, int mode, const za::SweepArgs& a);
 void launch_y_general(za_ctx* c, int mode, const za::SweepArgs& a);
 int general_y_blocks_per_cu(const za_problem& p);
 
+// Whether the environment leaves the resident 1D kernel on.
+bool resident_wanted();
+
 // Compute units of a device (256 if it cannot be asked).
 int device_cus(int device);
 

@@ -491,6 +491,21 @@ static za_status advance(za_ctx* c, double* q, int64_t* n, bool equal_steps, con
   return read_last || *n < all ? read_ctl(c, h) : ZA_OK;
 }
 
+// Set in the environment to 0.  ZA_STEP_GRAPHS=0 runs the steps of za_solve
+// as direct launches instead of replaying captured step graphs (results are
+// identical).
+static bool env_off(const char* name) {
+  const char* e = std::getenv(name);
+  return e && std::atoi(e) == 0;
+}
+
+// Whether steps may run in the resident 1D kernel: not with ZA_RESIDENT=0,
+// and not where the environment asks for a form of the step launches (results
+// are identical).
+bool resident_wanted() {
+  return !env_off("ZA_RESIDENT") && !env_off("ZA_STEP_GRAPHS") && !std::getenv("ZA_XL_CHUNKS");
+}
+
 // Everything a context derives from its problem without allocating: the
 // geometry and physics constants, launch shapes and reduction sizes.
 void init_shape(za_ctx* c, const za_problem* p, hipStream_t stream) {
@@ -523,16 +538,12 @@ void init_shape(za_ctx* c, const za_problem* p, hipStream_t stream) {
   fused_shape(*p, c->cus, &c->fu_gx, &c->fu_gy);
   c->ytile = pick_ytile(c);
   c->xl_chunks = pick_xl_chunks(c);
-  // ZA_STEP_GRAPHS=0 runs the steps of za_solve as direct launches instead
-  // of replaying captured step graphs (results are identical)
-  if (const char* e = std::getenv("ZA_STEP_GRAPHS")) c->graphs_ok = std::atoi(e) != 0;
-  // 1D problems that fit stay resident for many steps; ZA_RESIDENT=0, or
-  // either variable that selects a form of the step launches, turns that off
-  // (results are identical).  ZA_LINE_SPIN: the wait limit in clock ticks.
+  c->graphs_ok = !env_off("ZA_STEP_GRAPHS");
+  // 1D problems that fit stay resident for many steps.  ZA_LINE_SPIN: the wait
+  // limit in clock ticks.
   line_shape(*p, c->cus, &c->line_blocks, &c->line_waves);
-  const char* e = std::getenv("ZA_RESIDENT");
-  if ((e && std::atoi(e) == 0) || std::getenv("ZA_XL_CHUNKS") || std::getenv("ZA_STEP_GRAPHS")) c->line_blocks = 0;
-  if ((e = std::getenv("ZA_LINE_SPIN"))) c->line_spin = std::atoll(e);
+  if (!resident_wanted()) c->line_blocks = 0;
+  if (const char* e = std::getenv("ZA_LINE_SPIN")) c->line_spin = std::atoll(e);
 }
 
 // A right-hand side or flux sweep of q, whose speeds are in c->rows.

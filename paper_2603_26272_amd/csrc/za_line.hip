@@ -12,7 +12,9 @@ using namespace za;
 namespace {
 
 // Threads a block may have: FP64 Euler and the wide stencils need more than
-// the 128 registers that 1024 threads leave each.
+// the 128 registers that 1024 threads leave each.  (FP32 Euler with squared
+// weights spills 14 there; with 512 threads it is no faster up to 32,704 cells
+// and loses the lines beyond: 40,000 cells 8.0 -> 9.2 us a stage.)
 template <int SYS, class T, int WV, int R>
 constexpr int line_threads() {
   const bool wide = sizeof(T) == sizeof(double) && (SYS == SYS_EULER || R > 3 || WV != WV_Z1);

@@ -95,3 +95,16 @@ def test_pow_kernels_share_the_cu(kind, res):
     P = Problem(dim=2, nx=512, ny=512, **kind)
     assert _waves(P) == res
     assert _shape("fused_shape", P, 256) == _model(P, res)
+
+
+@pytest.mark.parametrize("env,on", [({}, True), (dict(ZA_STEP_GRAPHS="1"), True), (dict(ZA_STEP_GRAPHS="0"), False),
+                                    (dict(ZA_RESIDENT="1"), True), (dict(ZA_RESIDENT="0"), False),
+                                    (dict(ZA_XL_CHUNKS="3"), False)])
+def test_environment_that_leaves_the_resident_kernel_on(monkeypatch, env, on):
+    for k in ("ZA_RESIDENT", "ZA_STEP_GRAPHS", "ZA_XL_CHUNKS"):
+        monkeypatch.delenv(k, raising=False)
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    f = getattr(C.CDLL(za.LIB_PATH), "_Z15resident_wantedv")
+    f.restype = C.c_bool
+    assert f() is on
