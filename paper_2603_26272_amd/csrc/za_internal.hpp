@@ -33,12 +33,12 @@ struct za_ctx {
   hipGraphExec_t graph_exec = nullptr;  // GRAPH_STEPS steps for state graph_q
   const double* graph_q = nullptr;
   // resident 1D kernels (za_line.hpp): blocks and wavefronts per block (0:
-  // not for this problem), exchange words, the next launch's first tag, and
-  // the wait limit (< 0: default)
+  // not for this problem), exchange words, the next launch's first tag, the
+  // wait limit (< 0: default) and the first launch that it holds for
   int line_blocks = 0, line_waves = 0;
   unsigned long long* line_xch = nullptr;
   unsigned line_tag = 1;
-  long long line_spin = -1;
+  long long line_spin = -1, line_spin_from = 0, line_launches = 0;
   bool line_ok = true;       // false once a block waited too long
   bool timing = false;
   hipEvent_t ev_open[3] = {nullptr, nullptr, nullptr};

@@ -539,11 +539,15 @@ void init_shape(za_ctx* c, const za_problem* p, hipStream_t stream) {
   c->ytile = pick_ytile(c);
   c->xl_chunks = pick_xl_chunks(c);
   c->graphs_ok = !env_off("ZA_STEP_GRAPHS");
-  // 1D problems that fit stay resident for many steps.  ZA_LINE_SPIN: the wait
-  // limit in clock ticks.
+  // 1D problems that fit stay resident for many steps.  ZA_LINE_SPIN=ticks or
+  // ticks:n (tests): the wait limit of the launches, from the n-th (0: first) on.
   line_shape(*p, c->cus, &c->line_blocks, &c->line_waves);
   if (!resident_wanted()) c->line_blocks = 0;
-  if (const char* e = std::getenv("ZA_LINE_SPIN")) c->line_spin = std::atoll(e);
+  if (const char* e = std::getenv("ZA_LINE_SPIN")) {
+    char* end = nullptr;
+    c->line_spin = std::strtoll(e, &end, 10);
+    if (*end == ':') c->line_spin_from = std::atoll(end + 1);
+  }
 }
 
 // A right-hand side or flux sweep of q, whose speeds are in c->rows.

@@ -149,7 +149,8 @@ void launch_line(za_ctx* c, double* q, int64_t n, const DevCtl* init) {
   if (init) { a.init = *init; a.arm = 1; }
   a.nsteps = (int)n;
   a.tag0 = c->line_tag;
-  a.spin = c->line_spin >= 0 ? c->line_spin : kLineSpin;
+  a.spin = c->line_spin >= 0 && c->line_launches >= c->line_spin_from ? c->line_spin : kLineSpin;
+  ++c->line_launches;
   line_dispatch(c->prob, Solve{c, a});
   if (c->line_blocks > 1) {
     const size_t count = (size_t)c->m * c->prob.nx;

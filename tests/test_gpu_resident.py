@@ -181,3 +181,17 @@ def test_launches_after_a_long_wait_are_checked_as_often(monkeypatch):
         got = seconds(P, q0, T, ZA_LINE_SPIN="0")
         assert got[1] == ref[1] and np.array_equal(got[2], ref[2], equal_nan=True)
         assert got[0] < 4.0 * ref[0], (got[0], ref[0])
+
+
+@pytest.mark.parametrize("spin", [None, "0", "0:1"])
+@pytest.mark.parametrize("dt_rule", [0, 1])
+def test_several_launches_of_several_blocks(monkeypatch, dt_rule, spin):
+    """More steps than one launch takes (4096): the second launch goes on from
+    the control block that the first left, whether both run, the first gives
+    up, or the second does (the steps go back to where it began)."""
+    P, q0 = _data(EULER, 700)
+    P = P.with_(dt_rule=dt_rule)
+    if dt_rule == 0:
+        _same(monkeypatch, P, q0, steps=4500, spin=spin)
+    else:
+        _same(monkeypatch, P, q0, t_final=4500.4 * P.cfl * P.dx ** 2, steps=0, spin=spin)
