@@ -221,3 +221,43 @@ def test_injected_transfer_failure_ends_one_request(dev, monkeypatch, which):
     res = serve(reqs[:2])
     assert all(r[0] == 0 for r in res)
 
+
+
+def test_clients_submit_and_poll_while_bursts_run(dev):
+    """Four client threads submit requests of every class and poll them while
+    the scheduler launches bursts (with its lock released) and other requests
+    wait for a slot: each gets its own result, bit for bit the single
+    context's."""
+    import threading
+    import time
+    from paper_2603_26272_amd.za import Server
+    kinds = []
+    for i in range(4):
+        P2, q2 = W.quadrants_2d(70 + i, 90 + 17 * i, 75 + 5 * i)
+        P1, q1 = W.riemann_1d(80 + i, 600 + 211 * i)
+        kinds += [(P2, q2, 9 + i), (P2.fp32(), q2, 21), (P1, q1, 40 + i), (P1.fp32(), q1, 3 + i)]
+    refs = [ctx_solve(P, q0, n, dev) for P, q0, n in kinds]
+    errors = []
+    with Server(1 << 30, 6) as sv:
+        def client(c):
+            try:
+                for rnd in range(3):
+                    order = np.random.default_rng(10 * c + rnd).permutation(len(kinds))
+                    mine = [(int(k), sv.submit(*kinds[k])) for k in order]
+                    while mine:
+                        for k, rid in list(mine):
+                            done, st, q, stats = sv.poll(rid, kinds[k][0])
+                            if not done:
+                                continue
+                            mine.remove((k, rid))
+                            assert st == 0 and stats["steps"] == kinds[k][2]
+                            assert np.array_equal(q, refs[k]), (c, rnd, k)
+                        time.sleep(2e-4)
+            except BaseException as e:   # noqa: BLE001 (reported by the test's own thread)
+                errors.append(e)
+        th = [threading.Thread(target=client, args=(c,)) for c in range(4)]
+        [t.start() for t in th]
+        [t.join(90) for t in th]
+        assert not any(t.is_alive() for t in th)
+        sv.drain()
+    assert not errors, errors[0]
