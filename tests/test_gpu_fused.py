@@ -109,3 +109,75 @@ def test_wide_squared_kernels_agree_bitwise(order):
         out.append((rhs, q.cpu().numpy()))
     for a, b in zip(*out):
         assert np.array_equal(np.tile(a, (1, k, 1)), b)
+
+
+@pytest.mark.parametrize("kind", [dict(precision=1, eps=1e-20, mu0=1e-8),
+                                  dict(precision=1, eps=1e-20, mu0=1e-8, weight_L=0.0, p=2.0),
+                                  dict(precision=1, eps=1e-20, mu0=1e-8, p=1.5)], ids=["z", "js", "p15"])
+@pytest.mark.parametrize("bc", [TRANSMISSIVE, PERIODIC])
+def test_fp32_stages(kind, bc):
+    """One step with FP32 reconstruction (whose stages reload the FP64 state
+    for the update) at the edges of the tiles, against the oracle's FP32
+    reading and against the step put together from right-hand sides.
+
+    Oracle: each flux agrees to 3e-5 of its component scale S_F, so a stage's
+    update to 4 * 3e-5 * S_F dt / dx over both faces and directions, and the
+    step to three times that.  Right-hand sides: stage states that differ in
+    an FP64 rounding give the same FP32 records but where a value sits on a
+    rounding boundary; one such flip (2^-24) moves a flux by at most 8 * 2^-23
+    of its scale, hence 4 * 1e-6 * S_F dt / dx."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_26272_amd.za import Context
+    for nx, ny in SHAPES:
+        P, q0 = _data(nx, ny)
+        P = P.with_(bc_x=bc, bc_y=bc, **kind)
+        q = torch.from_numpy(q0).cuda()
+        with Context(P) as ctx:
+            dt = ctx.step(q, 0.0, sync=True)
+            L = lambda u: ctx.rhs(torch.from_numpy(u).cuda()).cpu().numpy()
+            q1 = q0 + dt * L(q0)
+            q2 = 0.75 * q0 + 0.25 * (q1 + dt * L(q1))
+            q3 = q0 / 3.0 + (2.0 / 3.0) * (q2 + dt * L(q2))
+        got = q.cpu().numpy()
+        ref, dt_ref, st = orc.step(P, q0, dt)
+        assert st == 0
+        fx, fy, _ = orc.fluxes(P, q0)
+        SF = np.maximum(np.abs(fx).max(axis=(1, 2), keepdims=True), np.abs(fy).max(axis=(1, 2), keepdims=True))
+        SQ = np.abs(q0).max(axis=(1, 2), keepdims=True)
+        unit = 4.0 * SF * dt / P.dx
+        assert (np.abs(got - ref) <= 3 * 3e-5 * unit + 1e-10 * SQ).all(), (nx, ny)
+        assert (np.abs(got - q3) <= 1e-6 * unit + 1e-13 * SQ).all(), (nx, ny)
+
+
+FLUX_KINDS = [dict(), dict(weight_L=0.0, p=2.0), dict(affine_invariant=1), dict(p=1.5), dict(alt_tau=1), dict(lf=1),
+              dict(linear_weights=1)] + [dict(order=r, **w) for r in (2, 4, 5)
+                                         for w in (dict(), dict(weight_L=0.0, p=2.0), dict(p=1.5))]
+
+
+@pytest.mark.parametrize("kind", FLUX_KINDS, ids=lambda k: "-".join(f"{a}{b}" for a, b in k.items()) or "z")
+def test_rhs_at_the_flux_bar(kind):
+    """The fused kernel has no flux output (za_rhs_fluxes runs the separate
+    sweeps), so its fluxes are held to their bar through the right-hand side:
+    every cell within what the bar of 1e-12 (|F| + max |F|) allows its four
+    faces, against the oracle's fluxes, and twice that against the library's
+    own flux output."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_26272_amd.za import Context
+    for (nx, ny), bc in (((63, 65), TRANSMISSIVE), ((130, 67), PERIODIC)):
+        P, q0 = W.quadrants_2d(nx * 7 + ny, nx, ny)
+        q0 = np.ascontiguousarray(q0)
+        q0[0] *= 1.0 + 1e-2 * np.random.default_rng(nx).random(q0[0].shape)   # rules out tied indicators
+        P = P.with_(bc_x=bc, bc_y=bc, **kind)
+        q = torch.from_numpy(q0).cuda()
+        with Context(P) as ctx:
+            got = ctx.rhs(q).cpu().numpy()
+            own = [f.cpu().numpy() for f in ctx.rhs_fluxes(q)]
+        fx, fy, st = orc.fluxes(P, q0)
+        assert st == 0
+        bx, by = (1e-12 * (np.abs(f) + np.abs(f).max(axis=(1, 2), keepdims=True)) for f in (fx, fy))
+        bar = (bx[:, :, 1:] + bx[:, :, :-1]) / P.dx + (by[:, 1:, :] + by[:, :-1, :]) / P.dy
+        for k, (gx, gy) in ((1, (fx, fy)), (2, own)):
+            ref = -(gx[:, :, 1:] - gx[:, :, :-1]) / P.dx - (gy[:, 1:, :] - gy[:, :-1, :]) / P.dy
+            assert (np.abs(got - ref) <= k * bar).all(), (nx, ny, k, float((np.abs(got - ref) / bar).max()))
