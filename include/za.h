@@ -134,7 +134,12 @@ typedef struct {
  * way).  1D problems of up to some ten thousand cells run their steps in one
  * resident launch.  In the environment, read at this call, ZA_RESIDENT=0,
  * ZA_STEP_GRAPHS=0 (steps as direct launches, no captured graphs) and any
- * ZA_XL_CHUNKS select ordinary launches instead (identical results). */
+ * ZA_XL_CHUNKS select ordinary launches instead (identical results).  A line
+ * of several blocks (beyond some 500 to 1000 cells) runs resident only within
+ * za_solve, where its blocks wait for each other: each takes at most a quarter
+ * of the device, so four such solves at once fit.  If others keep a block from
+ * running for 1 s, that solve repeats the steps with ordinary launches, and
+ * the context keeps those until it is destroyed. */
 za_status za_ctx_create(const za_problem* problem, void* hip_stream, za_ctx** out);
 /* Not from the paper (resource management): synchronise the context's
  * stream, free its workspace and the context.  ZA_ERR_ARG for NULL. */
@@ -247,7 +252,9 @@ typedef struct {
 
 /* Not from the paper.  hbm_budget_bytes: cap on the summed footprint of
  * admitted requests (the server allocates one pool of that size, and a
- * pinned host staging pool of the same size, at most 1 GiB).
+ * pinned host staging pool of the same size, at most 1 GiB).  Beyond the
+ * budget it allocates 192 KiB of wave-speed rows per slot (48 KiB for each of
+ * the four classes: 1D or 2D, FP64 or FP32) and less than 1 MiB of tables.
  * max_slots: concurrent requests.  device: HIP device ordinal.  *out
  * receives the server (NULL on error). */
 za_status za_server_create(size_t hbm_budget_bytes, int32_t max_slots, int32_t device, za_server** out);

@@ -19,7 +19,7 @@ struct za_ctx {
   za::Phys ph;
   double* q1 = nullptr;      // RK3 stage 1 state
   double* q2 = nullptr;      // RK3 stage 2 state
-  double* lx = nullptr;      // 2D: x-sweep partial RHS
+  double* lx = nullptr;      // 2D paired sweeps: the x-sweep's partial stage
   double* part = nullptr;    // partial sums (za_conserved_sums); the allocation's start
   unsigned long long* rows = nullptr;   // wave-speed rows: a set per stage, the first current between steps
   za::DevCtl* ctl = nullptr; // device control block: a copy per stage, the first current between steps

@@ -106,12 +106,13 @@ __device__ __forceinline__ double scalar_df(double u, double a) {
 }
 
 // ---------------------------------------------------------------------------
-// Wave speeds: per block maxima of |u_n - c|, |u_n|, |u_n + c| per direction
-// (part[b][0..5] = ax0 ax1 ax3 ay0 ay1 ay3).  max(|u_n| + c) equals
+// Wave speeds: maxima of |u_n - c|, |u_n|, |u_n + c| per direction (six
+// numbers: ax0 ax1 ax3 ay0 ay1 ay3).  max(|u_n| + c) equals
 // max(|u_n - c|, |u_n + c|) exactly (c > 0; both round the same sum), so it
 // is not stored.  A non-finite or non-physical cell (rho <= 0, p <= 0) sets
-// slot 0 to +infinity, which the final reduction reports.  Maxima are exact
-// and order independent, so the result is deterministic.
+// the first to +infinity, which the stage that reads the maxima reports
+// (stage_begin).  Maxima are exact and order independent, so the result is
+// deterministic.
 // ---------------------------------------------------------------------------
 constexpr int NPART = 6;
 
@@ -468,9 +469,10 @@ struct CfgArg { WeightCfg<T> w; };
 // Stage bookkeeping.  A step is its three stage kernels (or pairs of sweeps)
 // and nothing else: the kernel that writes a state folds the state's
 // wave-speed maxima into SP_ROWS rows with atomics, and the first kernel of
-// the next stage reduces those rows itself, in every wavefront, and advances
-// the control block (every block computes it, block 0 stores it: cin ->
-// ctl, one copy per stage).  A separate one-block launch for this took
+// the next stage reduces those rows itself and advances the control block
+// (every block computes it, in one wavefront of a fused block and in every
+// wavefront of an x-sweep's; block 0 stores it: cin -> ctl, one copy per
+// stage).  A y-sweep reads what its x-sweep stored.  A separate one-block launch for this took
 // 5.3 us of a 2048^2 stage's 290 and 4.3 of a 128^2 stage's 25; here it takes
 // about 1 us behind the loads of a block's first rows.  Three sets of rows
 // rotate: read, written, cleared for the stage after.  (256 rows: with 64,
@@ -870,8 +872,7 @@ __device__ __forceinline__ void sweep_x_body(const SweepArgs& a, const CfgArg<T>
 // passes as the one-shot sweep with half its record passes.
 //   MODE_LX (2D): the partial stage ca Q^n + cb (Q + dt L_x).
 //   MODE_STAGE (1D): the whole RK3 stage, and the wave-speed maxima of the new
-//   states, one row of a.part per wavefront (row = global wavefront index;
-//   the ny * nseg live wavefronts fill rows 0 .. ny * nseg - 1).
+//   states (each wavefront folds its own into row wid % SP_ROWS of sp_out).
 // ---------------------------------------------------------------------------
 constexpr int XL_RING = 128;
 

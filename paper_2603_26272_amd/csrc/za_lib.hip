@@ -1,9 +1,10 @@
 // libza: host side of the C ABI declared in include/za.h.
 //
 // One context = one problem shape on one device and stream.  It owns the
-// RK3 stage states, the x-sweep partial RHS (2D), the wave-speed reduction
-// partials and the device control block (LF speeds, dt, t) that lets whole
-// RK3 steps run without host round trips.
+// RK3 stage states, the partial stage of paired sweeps (2D scalar laws and
+// limited Euler stages), the wave-speed rows, partial sums, the exchange words
+// of a resident line and the device control blocks (LF speeds, dt, t) that let
+// whole RK3 steps run without host round trips.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

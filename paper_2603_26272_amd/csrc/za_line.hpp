@@ -4,7 +4,7 @@
 // launch: at N = 4096 a stage's sweep takes 6 us and the reduction launch
 // that follows it 3.4 us, of which the fluxes are 1.4 us.  Here one launch
 // runs up to a.nsteps steps.  Per stage, launches before -> resident now:
-// advection 400 cells 7.7 -> 1.5 us, 1D Euler 200 cells 8.6 -> 2.5 us (one
+// advection 400 cells 7.7 -> 1.3 us, 1D Euler 200 cells 8.6 -> 2.5 us (one
 // block: 2,900 cycles of fluxes, which four wavefronts on one CU issue at
 // 4.9 cycles per instruction, and 1,800 of update, records and reduction),
 // 1D Euler 4096 cells 9.7 -> 4.2 us (17 blocks: 2 us of it the round trip of
@@ -22,7 +22,10 @@
 // publishes after it has read this one.  Every wait is bounded by a.spin
 // ticks of the 100 MHz clock: a block that waits longer marks ctl->stuck and
 // ends, the others follow, the result (in a workspace) is not committed, and
-// the host repeats the steps with ordinary launches.
+// the host repeats the steps with ordinary launches, which the context keeps
+// from then on.  The limit is 1 s: the clock also runs while the device serves
+// other processes, and a line that gave up too soon would lose its speed for
+// good.
 #pragma once
 #include "za_kernels.hpp"
 
