@@ -10,8 +10,8 @@
 // in LDS.
 //
 // Bound: FP64 vector issue (690 of 800 instructions per interface) and, over
-// milliseconds, the board's power: data that vary everywhere run a quarter
-// slower than constant quadrants.  Against an x-sweep that wrote a partial
+// milliseconds, the board's power: data that vary everywhere run an eighth
+// slower than constant quadrants (2.01 against 2.30 GHz).  Against an x-sweep that wrote a partial
 // stage and a y-sweep that read it, HBM traffic per cell and stage falls from
 // 181 to 85 bytes, records are built once, and a stage is one launch.  Per
 // stage, before -> now (with the separate reduction launch before): 2048^2
