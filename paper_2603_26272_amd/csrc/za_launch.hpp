@@ -23,7 +23,11 @@ static void launch_x_t(za_ctx* c, int mode, SweepArgs a) {
     }
   }
   if (mode == MODE_FLUX) {
-    hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg);
+    if constexpr (SYS == SYS_EULER && M == 4 && WV == WV_GENERAL && sizeof(T) == sizeof(float))
+      // five wavefronts per SIMD: 97 registers where 96 give them
+      hipLaunchKernelGGL((k_sweep_x_r<SYS, M, T, MODE_FLUX, WV, 3, 5>), grid, blk, 0, c->stream, a, cfg);
+    else
+      hipLaunchKernelGGL((k_sweep_x_any<SYS, M, T, MODE_FLUX, WV>), grid, blk, 0, c->stream, a, cfg);
     return;
   }
   if constexpr (M != 4) {

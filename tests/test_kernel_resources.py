@@ -79,3 +79,8 @@ def test_1d_euler_sweeps_of_pow_weights_keep_their_wavefronts(kernels, mode, r, 
     assert hits
     for k in hits:
         assert _waves(k) >= waves and k[".private_segment_fixed_size"] == 0, k[".vgpr_count"]
+
+
+def test_fp32_flux_sweep_of_pow_weights_holds_five_wavefronts(kernels):
+    hits = [k for n, k in kernels.items() if "k_sweep_x_" in n and "<1, 4, float, 0, 1, 3" in n]
+    assert hits and all(_waves(k) >= 5 and k[".private_segment_fixed_size"] == 0 for k in hits)
