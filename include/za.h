@@ -151,7 +151,11 @@ za_status za_ctx_set_stream(za_ctx* ctx, void* hip_stream);
  * eq:hyperbolic_1D_scalar_h (0 if the problem is invalid). */
 size_t    za_state_count(const za_problem* problem);
 /* Not from the paper (admission control): device bytes the context
- * allocates for this problem, at most (0 if the problem is invalid). */
+ * allocates for this problem, at most (0 if the problem is invalid).  Not
+ * counted: what the HIP runtime sets aside for itself, which is the code and,
+ * per stream, up to 64 MB of private memory for the kernels that use it (large
+ * 2D Euler grids with squared weights at r = 4 or, at r = 2 and 4, with other
+ * exponents; 1D Euler with FP32 reconstruction and squared weights). */
 size_t    za_workspace_bytes(const za_problem* problem);
 
 /* rhs = L(q) = -(F_{i+1/2} - F_{i-1/2})/dx [- (G_{j+1/2} - G_{j-1/2})/dy]

@@ -26,7 +26,9 @@ int fused_waves(const za_problem& p) {
 // 4 s - 1 rows.  n resident blocks per CU take n s steps of a CU's issue
 // slots, times 1.5 for n = 1 and 1.15 for n = 2, which leave slots idle; a
 // round of blocks adds 2 steps for its start (first loads and records) and
-// the launch 1 more.  (Fitted over grids from 400^2 to 2048^2: FP64 stages
+// the launch 1 more.  Kernels of one block per CU take three to five times as
+// long over a step and half a step to start (2048^2, r = 5, squared weights:
+// 1207 us with four rounds of 17 steps, 1229 with two of 35).  (Fitted over grids from 400^2 to 2048^2: FP64 stages
 // take 9.5 us + 3.2 us per step; 1300 x 900: 76 us with the choice below, 98
 // with one block per CU.)  A strip takes whole wavefronts however narrow it
 // is: on grids of fewer than 8 columns (20 at r = 4, 5) an x-sweep and a
@@ -37,6 +39,7 @@ void fused_shape(const za_problem& p, int cus, int* gx, int* gy) {
   if (p.dim != 2 || p.system != ZA_EULER) return;
   const int res = fused_waves(p);   // resident blocks per CU of the kernel that p launches
   const int strips = (p.nx + FU_COLS - 1) / FU_COLS;
+  const double start = res == 1 ? 0.5 : 2.0;
   double best = -1;
   // (bands of more than 256 steps only where the grid would have too many)
   for (long long s = 1;; s = s < 256 ? s + 1 : 2 * s) {
@@ -46,7 +49,7 @@ void fused_shape(const za_problem& p, int cus, int* gx, int* gy) {
     const long long m = (strips * nb + cus - 1) / cus;
     const long long full = m / res, rest = m % res;
     const double idle = rest == 1 ? 1.5 : (rest == 2 && res > 2 ? 1.15 : 1.0);
-    const double cost = full * (res * s + 2.0) + (rest ? idle * rest * s + 2.0 : 0.0);
+    const double cost = full * (res * s + start) + (rest ? idle * rest * s + start : 0.0);
     if (best < 0 || cost < best) { best = cost; *gx = strips; *gy = (int)nb; }
     if (m <= 1 || s >= 256) break;   // from here on only slower
   }

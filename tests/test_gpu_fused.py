@@ -87,17 +87,18 @@ def test_bands_do_not_change_the_result():
             assert_close(got, np.tile(one, (1, k, 1)), 1e-12, f"{k} tiles")
 
 
-@pytest.mark.parametrize("order", [4, 5])
-def test_wide_squared_kernels_agree_bitwise(order):
-    """Squared weights at r = 4, 5 run one kernel where every block has a CU
-    of its own and another where blocks share CUs (more registers against
-    more blocks): a periodic tile gives the same bits through either."""
+@pytest.mark.parametrize("kind", [dict(order=4, weight_L=0.0, p=2.0), dict(order=4, p=1.5), dict(order=2, p=1.5)],
+                         ids=["r4-js", "r4-p15", "r2-p15"])
+def test_kernels_of_few_and_many_blocks_agree_bitwise(kind):
+    """Some weights run one kernel where few blocks share a CU and another, of
+    fewer registers, where many do: a periodic tile gives the same bits
+    through either."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2603_26272_amd.za import Context
     P, q0 = _data(128, 32)
-    P = P.with_(bc_x=PERIODIC, bc_y=PERIODIC, order=order, weight_L=0.0, p=2.0)
-    k = 64                                   # 33 blocks, then more than one per CU
+    P = P.with_(bc_x=PERIODIC, bc_y=PERIODIC, **kind)
+    k = 128                                  # 33 blocks, then more than two per CU
     Pk = P.with_(ny=32 * k, yhi=P.yhi * k)
     assert Pk.dy == P.dy
     out = []

@@ -56,17 +56,13 @@ def _waves(k):
     return min(8, 512 // (-(-k[".vgpr_count"] // 8) * 8))
 
 
-def _only(kernels, part):
-    hits = [k for n, k in kernels.items() if part in n]
-    assert hits, part
-    return hits
-
-
 # (weights: 1 with pow(), 2 powers of 1 and 2; r)
 @pytest.mark.parametrize("wv,r", [(1, 2), (1, 3), (2, 3), (2, 4)])
 @pytest.mark.parametrize("d", ["x", "y"])
 def test_flux_sweeps_of_general_weights_hold_two_wavefronts(kernels, d, wv, r):
-    for k in _only(kernels, f"k_sweep_{d}_any<1, 4, double, 0, {wv}, {r}>"):
+    hits = [k for n, k in kernels.items() if f"k_sweep_{d}_" in n and f"<1, 4, double, 0, {wv}, {r}" in n]
+    assert hits
+    for k in hits:
         assert _waves(k) >= 2, k[".vgpr_count"]
 
 
@@ -84,3 +80,17 @@ def test_1d_euler_sweeps_of_pow_weights_keep_their_wavefronts(kernels, mode, r, 
 def test_fp32_flux_sweep_of_pow_weights_holds_five_wavefronts(kernels):
     hits = [k for n, k in kernels.items() if "k_sweep_x_" in n and "<1, 4, float, 0, 1, 3" in n]
     assert hits and all(_waves(k) >= 5 and k[".private_segment_fixed_size"] == 0 for k in hits)
+
+
+def test_scratch_memory_stays_small(kernels):
+    """The runtime sets scratch aside per queue for a full device (8192
+    wavefronts of 64 lanes): at most 128 bytes per lane, 64 MB, in any kernel,
+    and in the fused stages none but for launches whose blocks share CUs."""
+    fused = {}
+    for n, k in kernels.items():
+        assert k[".private_segment_fixed_size"] <= 128, (n, k[".private_segment_fixed_size"])
+        if "k_fused<" in n:
+            T, wv, r, mode, w = [x.strip() for x in n.split("k_fused<")[1].split(">")[0].split(",")]
+            fused.setdefault((T, wv, r, mode), []).append((int(w), k[".private_segment_fixed_size"]))
+    for key, variants in fused.items():
+        assert min(variants)[1] == 0, (key, variants)

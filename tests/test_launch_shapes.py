@@ -55,7 +55,8 @@ def _model(P, res, cus=256):
         m = -(-strips * nb // cus)
         full, rest = divmod(m, res)
         idle = 1.5 if rest == 1 else (1.15 if rest == 2 and res > 2 else 1.0)
-        cost = full * (res * s + 2.0) + (idle * rest * s + 2.0 if rest else 0.0)
+        start = 0.5 if res == 1 else 2.0
+        cost = full * (res * s + start) + (idle * rest * s + start if rest else 0.0)
         if best is None or cost < best[0]:
             best = (cost, strips, nb)
         if m <= 1:
@@ -70,7 +71,7 @@ F32 = dict(precision=1, eps=1e-20, mu0=1e-8)
 @pytest.mark.parametrize("n", [64, 300, 512, 700, 1024, 2048])
 @pytest.mark.parametrize("kind,res", [(dict(), 3), (dict(order=2), 3), (dict(order=4), 2), (dict(order=5), 2),
                                       (JS, 2), (dict(order=2, **JS), 2), (dict(order=4, **JS), 2),
-                                      (dict(order=5, **JS), 2), (F32, 4), (dict(**F32, **JS), 3)])
+                                      (dict(order=5, **JS), 1), (F32, 4), (dict(**F32, **JS), 3)])
 def test_fused_bands_use_the_kernels_own_occupancy(kind, res, n):
     """The bands are those for as many resident blocks per CU as the kernel
     of these weights, this order and this precision is launched for."""
@@ -88,10 +89,11 @@ P15 = dict(p=1.5)
 
 
 @pytest.mark.parametrize("kind,res", [(dict(order=2, **P15), 3), (P15, 2), (dict(order=4, **P15), 2),
-                                      (dict(order=5, **P15), 2), (dict(**F32, **P15), 3)])
+                                      (dict(order=5, **P15), 1), (dict(**F32, **P15), 3)])
 def test_pow_kernels_share_the_cu(kind, res):
     """Weights with pow() leave most issue slots of a CU idle with one block:
-    the fused kernels are compiled, and their bands chosen, for several."""
+    the fused kernels are compiled, and their bands chosen, for several (but
+    at r = 5, where two would take too much scratch memory)."""
     P = Problem(dim=2, nx=512, ny=512, **kind)
     assert _waves(P) == res
     assert _shape("fused_shape", P, 256) == _model(P, res)
