@@ -60,7 +60,10 @@ void x_sys(za_ctx* c, int mode, SweepArgs a) {
 template <int SYS, int M, int R, int WV>
 void y_any(za_ctx* c, int mode, const SweepArgs& a, const CfgArg<double>& cfg, dim3 grid) {
   if (mode == MODE_FLUX) {
-    hipLaunchKernelGGL((k_sweep_y_any<SYS, M, double, MODE_FLUX, WV, R>), grid, dim3(256), 0, c->stream, a, cfg);
+    if constexpr (SYS == SYS_EULER && M == 4 && R == 2 && WV == WV_GENERAL)   // 171 registers, 168 give three
+      hipLaunchKernelGGL((k_sweep_y_r<SYS, M, double, MODE_FLUX, WV, R, 3>), grid, dim3(256), 0, c->stream, a, cfg);
+    else
+      hipLaunchKernelGGL((k_sweep_y_any<SYS, M, double, MODE_FLUX, WV, R>), grid, dim3(256), 0, c->stream, a, cfg);
     return;
   }
   if constexpr (M != 4) switch (mode) {

@@ -94,3 +94,8 @@ def test_scratch_memory_stays_small(kernels):
             fused.setdefault((T, wv, r, mode), []).append((int(w), k[".private_segment_fixed_size"]))
     for key, variants in fused.items():
         assert min(variants)[1] == 0, (key, variants)
+
+
+def test_flux_sweep_of_pow_weights_at_r2_holds_three_wavefronts(kernels):
+    hits = [k for n, k in kernels.items() if "k_sweep_y_" in n and "<1, 4, double, 0, 1, 2" in n]
+    assert hits and all(_waves(k) >= 3 and k[".private_segment_fixed_size"] == 0 for k in hits)
