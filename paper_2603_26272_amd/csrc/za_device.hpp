@@ -107,7 +107,7 @@ __device__ __forceinline__ void sqrt_rsq(float x, float& s, float& h) {
 // that kernel is 302 KB of code, far beyond the 64 KB instruction cache, and
 // takes 256 registers with 30 spilled; with calls 47 + 1.7 KB, 246 and none.
 // p = 3/2, us a stage, inlined -> called: 2048^2 r = 2 1590 -> 1447, r = 3
-// 2204 -> 2055, r = 5 4125 -> 3529; 128^2 r = 3 57 -> 53.  FP32 pow() is
+// 2204 -> 2055, r = 5 5620 -> 4959; 128^2 r = 3 57 -> 53.  FP32 pow() is
 // better inlined (1024^2 297 us, called 309).
 __device__ __attribute__((noinline)) inline double pow_call(double x, double e) { return pow(x, e); }
 

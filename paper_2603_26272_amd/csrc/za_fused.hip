@@ -26,14 +26,16 @@ int fused_waves(const za_problem& p) {
 // 4 s - 1 rows.  n resident blocks per CU take n s steps of a CU's issue
 // slots, times 1.5 for n = 1 and 1.15 for n = 2, which leave slots idle; a
 // round of blocks adds 2 steps for its start (first loads and records) and
-// the launch 1 more.  Kernels of one block per CU take three to five times as
-// long over a step and half a step to start (2048^2, r = 5, squared weights:
-// 1207 us with four rounds of 17 steps, 1229 with two of 35).  (Fitted over grids from 400^2 to 2048^2: FP64 stages
+// the launch 1 more.  (Fitted over grids from 400^2 to 2048^2: FP64 stages
 // take 9.5 us + 3.2 us per step; 1300 x 900: 76 us with the choice below, 98
-// with one block per CU.)  A strip takes whole wavefronts however narrow it
-// is: on grids of fewer than 8 columns (20 at r = 4, 5) an x-sweep and a
-// y-sweep that packs four rows of 16 columns are faster (4 x 100000: 257 us a
-// stage, fused 322), but there a state would not be the served one's bits.
+// with one block per CU.)  Kernels of one block per CU take three to five
+// times as long over a step, so half a step to start (2048^2, r = 5, squared
+// weights: 1207 us with four rounds of 17 steps, 1229 with two of 35).
+//
+// A strip takes whole wavefronts however narrow it is: on grids of fewer than
+// 8 columns (20 at r = 4, 5) an x-sweep and a y-sweep that packs four rows of
+// 16 columns are faster (4 x 100000: 257 us a stage, fused 322), but there a
+// state would not be the served one's bits.
 void fused_shape(const za_problem& p, int cus, int* gx, int* gy) {
   *gx = *gy = 0;
   if (p.dim != 2 || p.system != ZA_EULER) return;

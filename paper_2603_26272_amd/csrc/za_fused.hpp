@@ -11,13 +11,13 @@
 //
 // Bound: FP64 vector issue (690 of 800 instructions per interface) and, over
 // milliseconds, the board's power: data that vary everywhere run an eighth
-// slower than constant quadrants (2.01 against 2.30 GHz).  Against an x-sweep that wrote a partial
-// stage and a y-sweep that read it, HBM traffic per cell and stage falls from
-// 181 to 85 bytes, records are built once, and a stage is one launch.  Per
-// stage, before -> now (with the separate reduction launch before): 2048^2
-// FP64 277 -> 246 us, 512^2 39 -> 28 us, 128^2 24.7 -> 11.3 us; 2048^2 FP32
-// 208 -> 174 us; 512^2 JS weights (without pow()) 53 -> 42 us, tenth order 72
-// -> 65 us.
+// slower than constant quadrants (2.01 against 2.30 GHz).  Against an x-sweep
+// that wrote a partial stage and a y-sweep that read it, HBM traffic per cell
+// and stage falls from 181 to 85 bytes, records are built once, and a stage is
+// one launch.  Per stage, before -> now (with the separate reduction launch
+// before): 2048^2 FP64 277 -> 246 us, 512^2 39 -> 28 us, 128^2 24.7 -> 11.3 us;
+// 2048^2 FP32 208 -> 174 us; 512^2 JS weights (without pow()) 53 -> 42 us,
+// tenth order 72 -> 65 us.
 //
 // Shape.  64 x-interfaces take 63 columns; the y-interfaces of the same
 // columns leave one lane idle.  Four wavefronts per block, one per SIMD: of

@@ -472,12 +472,12 @@ struct CfgArg { WeightCfg<T> w; };
 // the next stage reduces those rows itself and advances the control block
 // (every block computes it, in one wavefront of a fused block and in every
 // wavefront of an x-sweep's; block 0 stores it: cin -> ctl, one copy per
-// stage).  A y-sweep reads what its x-sweep stored.  A separate one-block launch for this took
-// 5.3 us of a 2048^2 stage's 290 and 4.3 of a 128^2 stage's 25; here it takes
-// about 1 us behind the loads of a block's first rows.  Three sets of rows
-// rotate: read, written, cleared for the stage after.  (256 rows: with 64,
-// the 760 blocks of a 2048^2 stage queue at the same lines, 252 against
-// 246 us.)
+// stage).  A y-sweep reads what its x-sweep stored.  A separate one-block
+// launch for this took 5.3 us of a 2048^2 stage's 290 and 4.3 of a 128^2 stage's
+// 25; here it takes about 1 us behind the loads of a block's first rows.  Three
+// sets of rows rotate: read, written, cleared for the stage after.  (256 rows:
+// with 64, the 760 blocks of a 2048^2 stage queue at the same lines, 252
+// against 246 us.)
 //
 // A row holds NPART 64-bit keys (one 64-byte line), ordered like the numbers
 // they stand for; 0 is below every number.

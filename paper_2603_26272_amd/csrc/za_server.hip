@@ -335,7 +335,7 @@ static int serve_xl_chunks(const za_problem& p) {
 }
 
 // Bands of a 2D request, fixed at admission: of up to SERVE_STEPS steps, as
-// tall as leave the request a block per CU of the device (its latency when alone; taller
+// tall as leave the request a block per CU (its latency when alone; taller
 // ones in larger batches changed nothing).  ZA_SRV_YTILE in the environment
 // forces the rows of a band (rounded to a whole number of steps, at least
 // one).
